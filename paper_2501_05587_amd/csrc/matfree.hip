@@ -381,6 +381,311 @@ __global__ __launch_bounds__(256) void matfree_sweep(MfArgs a, Inst in, const in
     }
 }
 
+// ---------------------------------------------------------------- resident operand
+//
+// The same work item for rows of up to NS slabs of 128 bytes (FP32 d <= 256,
+// BF16 d <= 512, FP8 d <= 1024 with NS = 8): each wave keeps the fragments of
+// its 32 points in registers for the whole chunk and takes every position of
+// the tile, so only the positions' rows pass through LDS (MR rows at a time,
+// double-buffered, the next tile's rows and the one after's indices in flight
+// meanwhile).  With both operands staged per tile the sweep waited for gathered
+// rows with one workgroup per CU (241 VGPRs + 64 AGPRs); here a 32 x 32 block
+// needs 16 accumulators and no cross-wave flush, two to four workgroups share a
+// CU, and the bound is the vector ALU: per kernel value a sum of norms, a
+// multiply-add, a clamp, a multiply, a quarter-rate exponential and a sum.
+// Step at n = 50021, d = 128, k = 32, Gaussian, BF16: 4.15 -> 0.94 ms; at
+// n = 20000: BF16 d = 256 1.02 -> 0.38 ms, FP8 d = 256 0.94 -> 0.28 ms, FP32
+// d = 128 1.63 -> 1.03 ms and d = 256 2.66 -> 1.92 ms (the FP32 MFMA's rate).
+// Products run over the slabs in the staged kernel's order, so every kernel
+// value is bit for bit the one the stored K holds; the sums of 16 or 32 values
+// per lane go through the same compensated running sums.
+constexpr int MR_WAVE = 32;  // points per wave
+
+template <int NS> constexpr int mr_rows() { return NS <= 4 ? 64 : 32; }
+
+template <int NS> struct MrLds {
+    static constexpr int LD = NS * SLAB + 16;  // padded row: b128 reads of 32 rows spread over all banks
+    alignas(16) unsigned char op[2][mr_rows<NS>() * LD];
+    alignas(16) float rn[2][64], rs[2][64];    // norms / scales of the tile's positions
+};
+
+template <int PREC, int NS, int KERN>
+__global__ __launch_bounds__(256, NS <= 2 ? 3 : 2) void matfree_resident(MfArgs a, Inst in,
+                                                                        const int32_t *labels) {
+    constexpr int MR = mr_rows<NS>(), LD = MrLds<NS>::LD;
+    constexpr int RT = 8 * NS;                 // threads per row (16 bytes each)
+    constexpr int RP = (MR * RT + 255) / 256;  // 16-byte pieces per thread and tile
+    __shared__ MrLds<NS> lds;
+    if (*in.err != 0) return;
+    const int64_t n = in.n;
+    const int32_t k = in.k;
+    const int64_t item = blockIdx.x;
+    const int64_t strip = item % a.nstrip;
+    const int64_t q = item / a.nstrip;
+    // positions fit 32 bits (V's row pointers are int32)
+    const int32_t p_begin = (int32_t)(q * in.L);
+    const int32_t p_end = (int32_t)min(n, q * in.L + in.L);
+    const int32_t *__restrict__ perm = in.perm;
+    const int32_t *__restrict__ offsets = in.offsets;
+    const int nslab = (int)a.nslab;
+
+    const int tid = threadIdx.x;
+    const int lane = tid & 63;
+    const int wave = tid >> 6;
+    const int half = lane >> 5, l32 = lane & 31;
+    const int64_t wstrip = strip * (MF_N / MR_WAVE) + wave;  // 32-point strip of this wave
+    const int64_t my_i = wstrip * MR_WAVE + l32;
+    const bool in_n = my_i < n;
+    const int32_t my_lab = in_n ? labels[my_i] : -1;
+    const float nB = in_n ? a.nrm[my_i] : 0.f;
+    const float sB = (a.scale && in_n) ? a.scale[my_i] : 1.f;
+
+    // 16 bytes of a row.  Rows past the chunk or past n are read as the last one
+    // that exists, slabs past the row's as its first: their values are computed
+    // and left out of every sum, and no load waits on a branch.
+    auto piece = [&](int64_t row, int off) -> uint4 {
+        if constexpr (PREC == KKM_F32)
+            return __builtin_bit_cast(uint4, load_f32x4(a, row, off / 4));
+        else
+            return *reinterpret_cast<const uint4 *>(a.Xq + row * a.ldq_bytes +
+                                                    (off < nslab * SLAB ? off : off % SLAB));
+    };
+
+    // this wave's points: lane half h holds the 64 bytes at 64h of every slab
+    uint4 bfrag[NS][4];
+#pragma unroll
+    for (int sl = 0; sl < NS; ++sl)
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+            bfrag[sl][u] = piece(in_n ? my_i : n - 1, sl * SLAB + half * 64 + 16 * u);
+
+    // rows of a tile: 16-byte piece u of this thread lies in row row0 + RSTEP u
+    const int off0 = (tid % RT) * 16, row0 = tid / RT;
+    constexpr int RSTEP = 256 / RT;
+    static_assert(RSTEP * RP == MR, "the pieces cover the tile's rows exactly");
+    int32_t idx[RP], nidx = 0;
+    uint4 stage[RP];
+    float nst = 0.f, sst = 1.f;
+    auto load_idx = [&](int32_t p0) {
+#pragma unroll
+        for (int u = 0; u < RP; ++u) idx[u] = perm[min(p0 + row0 + RSTEP * u, p_end - 1)];
+        if (tid < MR) nidx = perm[min(p0 + tid, p_end - 1)];
+    };
+    auto load_rows = [&]() {
+#pragma unroll
+        for (int u = 0; u < RP; ++u) stage[u] = piece(idx[u], off0);
+        if (tid < MR) {
+            nst = a.nrm[nidx];
+            if (PREC == KKM_FP8_ROWSCALED) sst = a.scale[nidx];
+        }
+    };
+    auto store_rows_lds = [&](int buf) {
+#pragma unroll
+        for (int u = 0; u < RP; ++u)
+            *reinterpret_cast<uint4 *>(&lds.op[buf][(row0 + RSTEP * u) * LD + off0]) = stage[u];
+        if (tid < MR) {
+            lds.rn[buf][tid] = nst;
+            lds.rs[buf][tid] = sst;
+        }
+    };
+
+    // cluster holding position p_begin: last c with offsets[c] <= p_begin
+    int32_t lo = 0, hi = k - 1;
+    while (lo < hi) {
+        const int32_t mid = (lo + hi + 1) >> 1;
+        if (offsets[mid] <= p_begin) lo = mid;
+        else hi = mid - 1;
+    }
+    int32_t c = lo;
+    int32_t c_end = offsets[c + 1];
+
+    float run = 0.f, comp = 0.f;
+    auto flush = [&](int32_t cl) {
+        // lanes l and l + 32 hold the same point: fold the upper half in
+        const float os = __shfl_xor(run, 32, kWave);
+        const float oc = __shfl_xor(comp, 32, kWave);
+        float t, e;
+        two_sum(run, os, t, e);
+        const float tot = t + (comp + oc + e);
+        float z = 0.f;
+        if (half == 0 && in_n) {
+            in.P[(q + cl) * in.ldp + my_i] = tot;
+            if (my_lab == cl) z = tot;
+        }
+        z = wave_sum(z);
+        if (lane == 0 && wstrip < in.nws) in.Zp[(q + cl) * in.nws + wstrip] = z;
+        run = comp = 0.f;
+    };
+
+    load_idx(p_begin);
+    load_rows();
+    load_idx(p_begin + MR);
+    store_rows_lds(0);
+    __syncthreads();
+
+    // one 32 x 32 block of products of the tile in lds.op[buf], slabs in order
+    auto block_product = [&](int buf, int b) -> f32x16 {
+        f32x16 acc;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[r] = 0.f;
+        const unsigned char *As = &lds.op[buf][(32 * b + l32) * LD + half * 64];
+#pragma unroll
+        for (int sl = 0; sl < NS; ++sl) {
+            if (sl >= nslab) break;
+            uint4 av[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) av[u] = *reinterpret_cast<const uint4 *>(As + sl * SLAB + 16 * u);
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                if constexpr (PREC == KKM_BF16) {
+                    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
+                        __builtin_bit_cast(bf16x8, av[u]), __builtin_bit_cast(bf16x8, bfrag[sl][u]), acc,
+                        0, 0, 0);
+                } else if constexpr (PREC == KKM_FP8_ROWSCALED) {
+                    const long x0 = (long)(((uint64_t)av[u].y << 32) | av[u].x);
+                    const long x1 = (long)(((uint64_t)av[u].w << 32) | av[u].z);
+                    const long y0 = (long)(((uint64_t)bfrag[sl][u].y << 32) | bfrag[sl][u].x);
+                    const long y1 = (long)(((uint64_t)bfrag[sl][u].w << 32) | bfrag[sl][u].z);
+                    acc = __builtin_amdgcn_mfma_f32_32x32x16_fp8_fp8(x0, y0, acc, 0, 0, 0);
+                    acc = __builtin_amdgcn_mfma_f32_32x32x16_fp8_fp8(x1, y1, acc, 0, 0, 0);
+                } else {
+                    const f32x4 x = __builtin_bit_cast(f32x4, av[u]);
+                    const f32x4 y = __builtin_bit_cast(f32x4, bfrag[sl][u]);
+#pragma unroll
+                    for (int r = 0; r < 4; ++r)
+                        acc = __builtin_amdgcn_mfma_f32_32x32x2f32(x[r], y[r], acc, 0, 0, 0);
+                }
+            }
+        }
+        return acc;
+    };
+    // kernel values in place of the products: register r of lane l is position
+    // 8 (r/4) + 4 (l/32) + r%4 of block b, point l%32
+    auto block_kappa = [&](int buf, int b, f32x16 &acc) {
+        if constexpr (PREC == KKM_FP8_ROWSCALED) {
+#pragma unroll
+            for (int rg = 0; rg < 4; ++rg) {
+                const f32x4 sa = *reinterpret_cast<const f32x4 *>(&lds.rs[buf][32 * b + 8 * rg + 4 * half]);
+#pragma unroll
+                for (int r = 0; r < 4; ++r) acc[4 * rg + r] *= sa[r] * sB;
+            }
+        }
+        if constexpr (KERN == KKM_GAUSS) {
+#pragma unroll
+            for (int rg = 0; rg < 4; ++rg) {
+                const f32x4 na = *reinterpret_cast<const f32x4 *>(&lds.rn[buf][32 * b + 8 * rg + 4 * half]);
+#pragma unroll
+                for (int r = 0; r < 4; ++r)
+                    acc[4 * rg + r] = kappa_from_dot(acc[4 * rg + r], na[r], nB, KKM_GAUSS, a.gamma, 0.f, 1);
+            }
+        } else if constexpr (KERN == KKM_POLY) {
+            f32x16 t;
+#pragma unroll
+            for (int r = 0; r < 16; ++r) t[r] = acc[r] = fmaf(a.gamma, acc[r], a.coef0);
+            for (int g = 1; g < a.degree; ++g)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) acc[r] *= t[r];
+        }
+    };
+    auto block_sum = [&](const f32x16 &v) -> float {
+        float s4[4];
+#pragma unroll
+        for (int rg = 0; rg < 4; ++rg) s4[rg] = (v[4 * rg] + v[4 * rg + 1]) + (v[4 * rg + 2] + v[4 * rg + 3]);
+        return (s4[0] + s4[1]) + (s4[2] + s4[3]);
+    };
+    auto add_part = [&](float part) {
+        float t, e;
+        two_sum(run, part, t, e);
+        run = t;
+        comp += e;
+    };
+    // block b's positions [p, pt) cluster by cluster (the same for every lane)
+    auto block_segments = [&](const f32x16 &v, int32_t pb, int32_t pt) {
+        int32_t p = pb;
+        while (p < pt) {
+            while (c_end <= p) c_end = offsets[++c + 1];  // skip empty clusters
+            const int32_t seg_hi = min(pt, c_end);
+            float part = 0.f;
+            if (seg_hi - p == 32) {
+                part = block_sum(v);
+            } else {
+#pragma unroll
+                for (int r = 0; r < 16; ++r) {
+                    const int32_t m = pb + 8 * (r >> 2) + 4 * half + (r & 3);
+                    part += (m >= p && m < seg_hi) ? v[r] : 0.f;
+                }
+            }
+            add_part(part);
+            if (seg_hi == c_end || seg_hi == p_end) flush(c);
+            p = seg_hi;
+        }
+    };
+
+    int buf = 0;
+    for (int32_t p0 = p_begin; p0 < p_end; p0 += MR) {
+        const bool more = p0 + MR < p_end;
+        if (more) {
+            load_rows();
+            load_idx(p0 + 2 * MR);
+        }
+        if constexpr (MR == 64) {
+            // two blocks at a time: their products are independent MFMA chains,
+            // and a tile inside one cluster (the usual case) is summed at once
+            f32x16 v0 = block_product(buf, 0), v1 = block_product(buf, 1);
+            block_kappa(buf, 0, v0);
+            block_kappa(buf, 1, v1);
+            if (p0 + 64 < p_end && p0 + 64 < c_end) {
+                add_part(block_sum(v0) + block_sum(v1));
+            } else {
+                block_segments(v0, p0, min(p0 + 32, p_end));
+                if (p0 + 32 < p_end) block_segments(v1, p0 + 32, min(p0 + 64, p_end));
+            }
+        } else {
+            f32x16 v = block_product(buf, 0);
+            block_kappa(buf, 0, v);
+            block_segments(v, p0, min(p0 + 32, p_end));
+        }
+        if (more) {
+            store_rows_lds(buf ^ 1);
+            __syncthreads();  // the next tile is staged and every read of this one is done
+            buf ^= 1;
+        }
+    }
+}
+
+// Rows of up to 8 slabs stay resident (256 VGPRs; more would leave none for the
+// block's accumulators and the rows in flight; measured faster than staging
+// both operands over all of that range, 1.28x at FP32 d = 160 the least);
+// longer rows take the kernel that stages both.  Slabs of a row: SLAB bytes each.
+constexpr int64_t MR_MAX_SLABS = 8;
+int64_t mf_slabs(int64_t d, int32_t gram_prec) {
+    const int64_t eb = (gram_prec == KKM_F32) ? 4 : (gram_prec == KKM_BF16) ? 2 : 1;
+    return (d * eb + SLAB - 1) / SLAB;
+}
+
+template <int PREC, int KERN>
+void launch_resident_k(const MfArgs &a, const Inst &in, const int32_t *labels, int64_t items, hipStream_t st) {
+    const dim3 grid((unsigned)items), blk(256);
+    if (a.nslab <= 1)
+        hipLaunchKernelGGL((matfree_resident<PREC, 1, KERN>), grid, blk, 0, st, a, in, labels);
+    else if (a.nslab <= 2)
+        hipLaunchKernelGGL((matfree_resident<PREC, 2, KERN>), grid, blk, 0, st, a, in, labels);
+    else if (a.nslab <= 4)
+        hipLaunchKernelGGL((matfree_resident<PREC, 4, KERN>), grid, blk, 0, st, a, in, labels);
+    else
+        hipLaunchKernelGGL((matfree_resident<PREC, 8, KERN>), grid, blk, 0, st, a, in, labels);
+}
+
+template <int PREC>
+void launch_resident(const MfArgs &a, const Inst &in, const int32_t *labels, int64_t items, hipStream_t st) {
+    if (a.kernel == KKM_GAUSS)
+        launch_resident_k<PREC, KKM_GAUSS>(a, in, labels, items, st);
+    else if (a.kernel == KKM_POLY)
+        launch_resident_k<PREC, KKM_POLY>(a, in, labels, items, st);
+    else
+        launch_resident_k<PREC, KKM_LINEAR>(a, in, labels, items, st);
+}
+
 // Squared norm of each FP32 row (one wave per row).
 __global__ __launch_bounds__(256) void mf_sqnorms(const float *X, int64_t n, int64_t d, int64_t ldx,
                                                   float *nrm) {
@@ -429,6 +734,8 @@ int64_t mf_chunk(int64_t n) {
 struct MfLayout {
     InstGeom g;
     int64_t nstrip, dpad;
+    bool resident;  // the sweep that keeps the points' rows in registers
+    int64_t nws;    // own-cluster sums per slot: one per wave (32 points) or per strip
     size_t inst_bytes, zp_floats, xq_bytes;
 };
 
@@ -438,7 +745,9 @@ MfLayout mf_layout(int64_t n, int64_t d, int32_t k, int32_t gram_prec) {
     m.nstrip = (n + MF_N - 1) / MF_N;
     m.dpad = (gram_prec == KKM_F32) ? d : padded_d(d, gram_prec);
     m.inst_bytes = inst_workspace_bytes(m.g);
-    m.zp_floats = (size_t)m.g.slots * (size_t)m.nstrip;
+    m.resident = mf_slabs(d, gram_prec) <= MR_MAX_SLABS;
+    m.nws = m.resident ? (n + MR_WAVE - 1) / MR_WAVE : m.nstrip;
+    m.zp_floats = (size_t)m.g.slots * (size_t)m.nws;
     m.xq_bytes = (gram_prec == KKM_F32) ? 0
                  : (size_t)n * (size_t)m.dpad * ((gram_prec == KKM_BF16) ? 2 : 1);
     return m;
@@ -479,6 +788,7 @@ kkm_status mf_prologue(const float *X, int64_t n, int64_t d, int64_t ldx, int32_
     r.nrm = w.nrm;
     r.scale = nullptr;
     r.nstrip = m.nstrip;
+    r.nslab = mf_slabs(d, gram_prec);
     if (gram_prec == KKM_F32) {
         hipLaunchKernelGGL(mf_sqnorms, dim3(qgrid), dim3(256), 0, s, X, n, d, ldx, w.nrm);
     } else {
@@ -520,7 +830,7 @@ kkm_status mf_step(const MfArgs &a, int32_t gram_prec, const MfLayout &m, const 
     in.D_out = D_out;
     in.ctilde_out = ctilde_out;
     in.nstrip = m.nstrip;
-    in.nws = m.nstrip;
+    in.nws = m.nws;
     in.Zp = w.Zp;
     const int64_t items = m.nstrip * m.g.nchunk;
     if (items > 0x7fffffff) {
@@ -530,7 +840,13 @@ kkm_status mf_step(const MfArgs &a, int32_t gram_prec, const MfLayout &m, const 
     auto sweep = [&](hipStream_t st) -> kkm_status {
         const dim3 grid((unsigned)items), blk(256);
         const TimedSpan span = timing_begin(TK_SWEEP, st);
-        if (gram_prec == KKM_F32)
+        if (m.resident && gram_prec == KKM_F32)
+            launch_resident<KKM_F32>(a, in, labels_in, items, st);
+        else if (m.resident && gram_prec == KKM_BF16)
+            launch_resident<KKM_BF16>(a, in, labels_in, items, st);
+        else if (m.resident)
+            launch_resident<KKM_FP8_ROWSCALED>(a, in, labels_in, items, st);
+        else if (gram_prec == KKM_F32)
             hipLaunchKernelGGL(matfree_sweep<KKM_F32>, grid, blk, 0, st, a, in, labels_in);
         else if (gram_prec == KKM_BF16)
             hipLaunchKernelGGL(matfree_sweep<KKM_BF16>, grid, blk, 0, st, a, in, labels_in);

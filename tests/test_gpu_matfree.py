@@ -131,6 +131,24 @@ def test_matfree_learned_workload_prefix(kkm, prec):
                    prec=prec, what="learned100k[:4100] prec %d" % prec)
 
 
+# row lengths at the edges of the sweep that keeps the points' rows in registers
+# (1, 2, 3, 4, 5 and 8 slabs of 128 bytes) and one slab past it, with clusters
+# that end inside 32-position blocks, at their edges and across tiles
+@pytest.mark.parametrize("prec,d", [(0, 32), (0, 33), (0, 128), (0, 129), (0, 256), (0, 257),
+                                    (1, 64), (1, 65), (1, 192), (1, 256), (1, 257), (1, 513),
+                                    (2, 128), (2, 129), (2, 1024), (2, 1025)])
+def test_matfree_row_length_edges(kkm, prec, d):
+    rng = np.random.default_rng(7000 + 10 * d + prec)
+    n, k = 449, 6
+    X = rng.normal(0, 1, (n, d)).astype(np.float32)
+    sizes = [64, 1, 128, 31, 0, 225]  # cluster 4 is empty
+    labels = rng.permutation(np.repeat(np.arange(k), sizes)).astype(np.int32)
+    teacher_forced(kkm, X, datagen.GAUSS, 0.5 / d, 0.0, 1, k, labels, 1, prec=prec,
+                   what="prec %d d %d" % (prec, d))
+    teacher_forced(kkm, X, datagen.POLY, 1.0 / d, 1.0, 3, k, labels, 1, prec=prec,
+                   empty_policy=1, what="poly prec %d d %d" % (prec, d))
+
+
 # ragged n over one to several 128-point strips and 128-position chunks, odd d
 @pytest.mark.parametrize("n,d,k", [(1, 2, 1), (7, 3, 2), (65, 4, 7), (129, 33, 5), (1025, 5, 3),
                                    (2049, 70, 33), (3000, 6, 1)])
