@@ -24,7 +24,6 @@ struct Inst {
     // workspace
     int32_t *perm, *offsets, *counts, *blk_hist, *blk_bad, *err;
     float *P, *Zp, *ctilde;
-    double *Jpart;
     // outputs of the step
     int32_t *counts_out;
     int64_t *n_changed;
@@ -82,7 +81,7 @@ int64_t inst_sweep_items(const InstGeom &g, int32_t k_store);
 // Sets the strip counts that depend on the element type of K.
 void inst_set_store(Inst *in, int32_t k_store);
 
-// The seven kernels of one step over the whole set.  total_blocks,
+// One step over the whole set (seven kernels; three for one small problem).  total_blocks,
 // total_clusters and sweep_grid are grid sizes: label blocks, clusters and
 // sweep items summed over every problem the set can hold; max_k sizes the
 // dynamic LDS; vec: every K row is 16-byte aligned.

@@ -35,7 +35,10 @@ namespace {
 
 constexpr int kPtsPerBlock = 256;          // points per block in the label kernels
 constexpr int kSweepThreads = 256;         // 4 waves
-constexpr int kSlotWindow = 1024;          // slot -> cluster entries per LDS window
+constexpr int kAssignPts = 64;             // points per assignment workgroup (4 waves share them)
+constexpr int kAssignStageK = 128;         // largest k whose D rows are staged in LDS
+constexpr int kSmallThreads = 1024;        // the one-workgroup CSR build
+constexpr int64_t kSmallPts = 8192;        // its most points
 
 // The problem and the block index within it for a flattened grid position g;
 // false when g lies past the live problems of a table.  MULTI selects the
@@ -57,6 +60,21 @@ __device__ __forceinline__ bool locate(const InstSet &s, const int64_t *start, i
 }
 
 // ---------------------------------------------------------------- 1. V in CSR form
+
+// Bits needed for labels in [0, k).
+__device__ __forceinline__ int label_bits(int32_t k) { return k > 1 ? 32 - __clz(k - 1) : 0; }
+
+// The wave's valid lanes holding the same label as this one: one ballot per
+// label bit (a ballot per distinct label took up to min(k, 64) rounds).
+__device__ __forceinline__ uint64_t label_peers(bool valid, int32_t c, int bits) {
+    uint64_t peers = __ballot(valid);
+    for (int b = 0; b < bits; ++b) {
+        const bool one = (c >> b) & 1;
+        const uint64_t m = __ballot(one);
+        peers &= one ? m : ~m;
+    }
+    return peers;
+}
 
 // Per-block label histogram (column-major [k][nblk]) and range check.
 template <bool MULTI>
@@ -165,20 +183,10 @@ __global__ __launch_bounds__(kPtsPerBlock) void v_scatter(InstSet s, const int32
     const int64_t i = lb * kPtsPerBlock + tid;
     const bool valid = i < in.n;
     const int32_t c = valid ? labels[i] : -1;
-    // rank among equal labels earlier in this wave, by matching label groups
-    uint64_t pending = __ballot(valid);
-    int32_t rank = 0;
-    while (pending) {
-        const int leader = __ffsll((unsigned long long)pending) - 1;
-        const int32_t lc = __shfl(c, leader, kWave);
-        const uint64_t m = __ballot(valid && c == lc);
-        if (valid && c == lc) {
-            const uint64_t below = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
-            rank = __popcll(m & below);
-            if (lane == leader) wcnt[wave * k + c] = __popcll(m);
-        }
-        pending &= ~m;
-    }
+    // rank among equal labels earlier in this wave
+    const uint64_t peers = label_peers(valid, c, label_bits(k));
+    const int32_t rank = __popcll(peers & ((lane == 0) ? 0ull : (~0ull >> (64 - lane))));
+    if (valid && rank == 0) wcnt[wave * k + c] = __popcll(peers);
     __syncthreads();
     if (valid) {
         int32_t before = 0;
@@ -186,6 +194,94 @@ __global__ __launch_bounds__(kPtsPerBlock) void v_scatter(InstSet s, const int32
         const int64_t pos = off[c] + in.blk_hist[(int64_t)c * in.nblk + lb] + before + rank;
         in.perm[pos] = (int32_t)i;
     }
+}
+
+// The three kernels above in one workgroup, for one small problem: below about
+// 8000 points each of them is a launch whose few workgroups wait on memory
+// (2.5 + 4.1 + 3.4 us and their gaps at n = 1000; here 3.6).  Each wave takes a contiguous
+// stretch of points, 64 at a time, so its running counts need no barrier; the
+// labels are read once.  Same row pointers and the same stable order, so the
+// same V.
+constexpr int kSmallGroups = kSmallPts / kSmallThreads;  // 64-point groups per wave
+
+__global__ __launch_bounds__(kSmallThreads) void v_csr_small(Inst in, const int32_t *labels) {
+    extern __shared__ int32_t sh[];  // run[k], wcnt[16][k]
+    __shared__ int32_t bad;
+    const int32_t k = in.k;
+    const int32_t n = (int32_t)in.n;
+    constexpr int NW = kSmallThreads / kWave;
+    int32_t *run = sh, *wcnt = sh + k;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int groups = (n + kSmallThreads - 1) / kSmallThreads;
+    const int32_t i0 = wave * groups * kWave + lane;
+    int32_t c[kSmallGroups], rank[kSmallGroups];
+#pragma unroll
+    for (int g = 0; g < kSmallGroups; ++g) {
+        const int32_t i = i0 + g * kWave;
+        c[g] = (g < groups && i < n) ? labels[i] : -1;
+    }
+    for (int t = tid; t < NW * k; t += kSmallThreads) wcnt[t] = 0;
+    if (tid == 0) bad = 0;
+    __syncthreads();
+    const int bits = label_bits(k);
+    int32_t nbad = 0;
+#pragma unroll
+    for (int g = 0; g < kSmallGroups; ++g) {
+        if (g >= groups) break;
+        const bool in_n = i0 + g * kWave < n;
+        const bool valid = in_n && c[g] >= 0 && c[g] < k;
+        nbad += __popcll(__ballot(in_n && !valid));
+        const uint64_t peers = label_peers(valid, c[g], bits);
+        const int32_t below = __popcll(peers & ((lane == 0) ? 0ull : (~0ull >> (64 - lane))));
+        if (valid) {
+            const int32_t before = wcnt[wave * k + c[g]];  // read by the group's lanes,
+            rank[g] = before + below;
+            if (below == 0) wcnt[wave * k + c[g]] = before + __popcll(peers);  // then its first writes
+        }
+    }
+    if (nbad && lane == 0) atomicAdd(&bad, nbad);
+    __syncthreads();
+    nbad = bad;
+    if (tid == 0) {
+        in.err[0] = nbad;
+        in.err[1] = 0;  // the assignment's arrival counter
+    }
+    if (nbad != 0) return;  // uniform
+    for (int t = tid; t < k; t += kSmallThreads) {
+        int32_t sum = 0;
+#pragma unroll
+        for (int w = 0; w < NW; ++w) {
+            const int32_t v = wcnt[w * k + t];
+            wcnt[w * k + t] = sum;
+            sum += v;
+        }
+        run[t] = sum;
+    }
+    __syncthreads();
+    // sizes -> exclusive prefix (row pointers), one wave
+    if (wave == 0) {
+        int32_t base = 0;
+        for (int32_t t0 = 0; t0 < k; t0 += kWave) {
+            const int32_t v = (t0 + lane < k) ? run[t0 + lane] : 0;
+            int32_t x = v;
+#pragma unroll
+            for (int off = 1; off < kWave; off <<= 1) {
+                const int32_t y = __shfl_up(x, off, kWave);
+                if (lane >= off) x += y;
+            }
+            if (t0 + lane < k) {
+                run[t0 + lane] = base + x - v;
+                in.offsets[t0 + lane] = base + x - v;
+            }
+            base += __shfl(x, kWave - 1, kWave);
+        }
+        if (lane == 0) in.offsets[k] = base;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int g = 0; g < kSmallGroups; ++g)
+        if (g < groups && i0 + g * kWave < n)
+            in.perm[run[c[g]] + wcnt[wave * k + c[g]] + rank[g]] = i0 + g * kWave;
 }
 
 // ---------------------------------------------------------------- 2. row sweep of K
@@ -408,11 +504,158 @@ __global__ __launch_bounds__(kSweepThreads) void spmm_row_sweep(InstSet s,
     sweep_item<T, VEC>(in, item, labels_all);
 }
 
+// The sweep of a small problem: one workgroup per (64 E columns, chunk of at
+// most 64 positions), its eight waves taking the chunk's blocks of up to eight
+// rows in turn; wave 0 then adds the block sums, segment by segment, in their
+// order.  Blocks, order and compensation are sweep_item's, so the partial sums
+// are the same bit for bit.  sweep_item walks the chunk in one wave, a chain of
+// index and row loads of which a small K has too few workgroups to hide
+// (n = 1000: 16 workgroups, 18 us, here 7.9; n = 3001: 38 us for 36 MB, here 12).
+constexpr int kSmallWaves = 8;    // (16: 2 workgroups per CU, n = 3001 12.0 -> 14.7 us)
+constexpr int kSmallBlocks = 16;  // block sums staged per round
+
+template <typename T, bool VEC>
+__global__ __launch_bounds__(kSmallWaves *kWave) void spmm_small_sweep(Inst in, const int32_t *labels) {
+    constexpr int E = KRow<T>::E;
+    __shared__ __attribute__((aligned(16))) float bs[kSmallBlocks][kWave * E];
+    __shared__ int32_t offsets[KKM_MAX_K + 1];
+    const int64_t n = in.n;
+    const T *__restrict__ K = static_cast<const T *>(in.K);
+    const int64_t ldk = in.ldk;
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int64_t strip = (uint32_t)blockIdx.x % (uint32_t)in.nws;
+    const int64_t q = (uint32_t)blockIdx.x / (uint32_t)in.nws;
+    const int64_t col = strip * (kWave * E) + (int64_t)lane * E;
+    const int32_t p_begin = (int32_t)(q * in.L);
+    const int32_t p_end = (int32_t)min(n, q * in.L + in.L);
+    const uint32_t voff = (uint32_t)(col * (int64_t)sizeof(T));
+    const uint32_t rbytes = (uint32_t)(ldk * (int64_t)sizeof(T));
+    // the chunk's rows (at most 64), one per lane
+    const int32_t bad = *in.err;
+    const int32_t rows = in.perm[min(p_begin + lane, p_end - 1)];
+    for (int t = threadIdx.x; t <= in.k; t += kSmallWaves * kWave) offsets[t] = in.offsets[t];
+    if (bad != 0) return;
+    int32_t own[E];
+#pragma unroll
+    for (int u = 0; u < E; ++u) own[u] = (wave == 0 && col + u < n) ? labels[col + u] : -1;
+    __syncthreads();
+    // cluster holding position p_begin: last c with offsets[c] <= p_begin
+    int32_t lo = 0, hi = in.k - 1;
+    while (lo < hi) {
+        const int32_t mid = (lo + hi + 1) >> 1;
+        if (__builtin_amdgcn_readfirstlane(offsets[mid]) <= p_begin) lo = mid;
+        else hi = mid - 1;
+    }
+    int32_t c = lo;
+    auto end_of = [&](int32_t cl) { return __builtin_amdgcn_readfirstlane(offsets[cl + 1]); };
+    int32_t c_end = end_of(c);
+
+    float sum[E], e[E];
+#pragma unroll
+    for (int u = 0; u < E; ++u) sum[u] = e[u] = 0.f;
+    int32_t p = p_begin;
+    while (p < p_end) {
+        // this round's blocks: up to eight rows of one segment each
+        int32_t pr = p, cr = c, cr_end = c_end, nb = 0;
+        while (pr < p_end && nb < kSmallBlocks) {
+            while (cr_end <= pr) cr_end = end_of(++cr);  // skip empty clusters
+            const int32_t cnt = min(8, min(p_end, cr_end) - pr);
+            if ((nb & (kSmallWaves - 1)) == wave) {
+                float blk[E];
+                const int l0 = pr - p_begin;
+                if (cnt == 8) {
+                    float v[8][E];
+#pragma unroll
+                    for (int r = 0; r < 8; ++r) {
+                        const int64_t j = __builtin_amdgcn_readlane(rows, l0 + r);
+                        load_row<T, VEC>(K + j * ldk, col, n, voff, rbytes, v[r]);
+                    }
+#pragma unroll
+                    for (int u = 0; u < E; ++u) {
+                        const float h0 = (v[0][u] + v[1][u]) + (v[2][u] + v[3][u]);
+                        const float h1 = (v[4][u] + v[5][u]) + (v[6][u] + v[7][u]);
+                        blk[u] = h0 + h1;
+                    }
+                } else {
+#pragma unroll
+                    for (int u = 0; u < E; ++u) blk[u] = 0.f;
+                    for (int r = 0; r < cnt; ++r) {
+                        const int64_t j = __builtin_amdgcn_readlane(rows, l0 + r);
+                        float v[E];
+                        load_row<T, VEC>(K + j * ldk, col, n, voff, rbytes, v);
+#pragma unroll
+                        for (int u = 0; u < E; ++u) blk[u] += v[u];
+                    }
+                }
+#pragma unroll
+                for (int u = 0; u < E; u += 4)
+                    *reinterpret_cast<f32x4 *>(&bs[nb][lane * E + u]) =
+                        f32x4{blk[u], blk[u + 1], blk[u + 2], blk[u + 3]};
+            }
+            ++nb;
+            pr += cnt;
+        }
+        __syncthreads();
+        if (wave == 0) {
+            int32_t pw = p;
+            f32x4 ahead[E / 4];
+            auto fetch = [&](int b) {
+#pragma unroll
+                for (int u = 0; u < E / 4; ++u) ahead[u] = *reinterpret_cast<const f32x4 *>(&bs[b][lane * E + 4 * u]);
+            };
+            fetch(0);
+            for (int b = 0; b < nb; ++b) {
+                f32x4 v[E / 4];
+#pragma unroll
+                for (int u = 0; u < E / 4; ++u) v[u] = ahead[u];
+                fetch(min(b + 1, kSmallBlocks - 1));
+                while (c_end <= pw) c_end = end_of(++c);
+                const int32_t seg_end = min(p_end, c_end);
+                pw += min(8, seg_end - pw);
+#pragma unroll
+                for (int u = 0; u < E; ++u) {
+                    float t, er;
+                    two_sum(sum[u], v[u / 4][u % 4], t, er);
+                    sum[u] = t;
+                    e[u] += er;
+                }
+                if (pw < seg_end) continue;
+                const int64_t slot = q + c;
+                float *dst = in.P + slot * in.ldp + col;
+                float tot[E];
+                float z = 0.f;
+#pragma unroll
+                for (int u = 0; u < E; ++u) {
+                    tot[u] = sum[u] + e[u];
+                    if (own[u] == c) z += tot[u];
+                    sum[u] = e[u] = 0.f;
+                }
+                if (col + E - 1 < n) {
+#pragma unroll
+                    for (int u = 0; u < E; u += 4)
+                        *reinterpret_cast<f32x4 *>(dst + u) = f32x4{tot[u], tot[u + 1], tot[u + 2], tot[u + 3]};
+                } else {
+#pragma unroll
+                    for (int u = 0; u < E; ++u)
+                        if (col + u < n) dst[u] = tot[u];
+                }
+                z = wave_sum(z);
+                if (lane == 0) in.Zp[slot * in.nws + strip] = z;
+            }
+        }
+        p = pr;
+        c = cr;
+        c_end = cr_end;
+        if (p < p_end) __syncthreads();  // the sums are read before the next round writes its own
+    }
+}
+
 // ---------------------------------------------------------------- 3. centroid norms
 
 // One workgroup per (problem, cluster): ||c_c||^2 = (1/|c|^2) sum_{i in c} S_ic,
 // summing the z partials of the cluster's segments in a fixed order.
-template <int E, bool MULTI>
+template <bool MULTI>
 __global__ __launch_bounds__(256) void centroid_norms(InstSet s) {
     __shared__ float ss[256], sc[256];
     Inst in;
@@ -426,13 +669,20 @@ __global__ __launch_bounds__(256) void centroid_norms(InstSet s) {
     if (cnt > 0) {
         const int64_t q0 = a / in.L, q1 = (e - 1) / in.L;
         const int64_t total = (q1 - q0 + 1) * nws;
-        for (int64_t t = threadIdx.x; t < total; t += 256) {
-            const int64_t q = q0 + t / nws;
-            const int64_t w = t % nws;
-            float u, er;
-            two_sum(sum, in.Zp[(q + c) * nws + w], u, er);
-            sum = u;
-            comp += er;
+        const float *z = in.Zp + (q0 + c) * nws;  // the cluster's slots follow each other
+        // eight loads at a time: few clusters mean few workgroups, each a chain
+        // of loads (n = 60000, k = 10: 17 -> 6.7 us)
+        for (int64_t t = threadIdx.x; t < total; t += 8 * 256) {
+            float v[8];
+#pragma unroll
+            for (int r = 0; r < 8; ++r) v[r] = (t + 256 * r < total) ? z[t + 256 * r] : 0.f;
+#pragma unroll
+            for (int r = 0; r < 8; ++r) {  // adding 0 past the end changes nothing
+                float u, er;
+                two_sum(sum, v[r], u, er);
+                sum = u;
+                comp += er;
+            }
         }
     }
     ss[threadIdx.x] = sum;
@@ -458,166 +708,335 @@ __global__ __launch_bounds__(256) void centroid_norms(InstSet s) {
     }
 }
 
+// The same norm by one wave, from the cluster's `total` own-cluster sums z:
+// lane l stands for the 256 threads' sums l, l + 64, l + 128 and l + 192, added
+// in the tree's order, so the bits are the same.  Lane 0 holds the result.
+__device__ __forceinline__ float cluster_norm_wave(const float *z, int32_t total, int32_t cnt, int lane) {
+    float s[4], m[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) s[u] = m[u] = 0.f;
+    for (int32_t t = 0; t < total; t += 256) {
+        float x[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) x[u] = (t + lane + 64 * u < total) ? z[t + lane + 64 * u] : 0.f;
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            float w, er;
+            two_sum(s[u], x[u], w, er);
+            s[u] = w;
+            m[u] += er;
+        }
+    }
+    auto join = [](float &s0, float &m0, float s1, float m1) {
+        float u, er;
+        two_sum(s0, s1, u, er);
+        s0 = u;
+        m0 += m1 + er;
+    };
+    join(s[0], m[0], s[2], m[2]);
+    join(s[1], m[1], s[3], m[3]);
+    join(s[0], m[0], s[1], m[1]);
+#pragma unroll
+    for (int h = kWave / 2; h > 0; h >>= 1) {
+        const float s1 = __shfl_down(s[0], h, kWave), m1 = __shfl_down(m[0], h, kWave);
+        join(s[0], m[0], s1, m1);
+    }
+    const float fc = (float)cnt;
+    return ((s[0] + m[0]) / fc) / fc;
+}
+
 // ---------------------------------------------------------------- 4. distances + argmin + histogram
 
-template <bool MULTI>
-__global__ __launch_bounds__(kPtsPerBlock) void assign_fused(InstSet s,
-                                                             const int32_t *labels_in_all,
-                                                             int32_t *labels_out_all) {
-    extern __shared__ int32_t sh[];  // off[k+1], hist[k], seg[kSlotWindow]
-    __shared__ double wJ[kPtsPerBlock / kWave];
-    __shared__ long long wC[kPtsPerBlock / kWave];
+// What each assignment workgroup leaves for the end of the step: its part of J
+// and of the changed labels, over V's column indices (the sweep was their last
+// reader), and its cluster sizes (at most 64: bytes) over the CSR build's block
+// histograms, [k][4 nblk].  Sums in a fixed order instead of atomics: with a
+// workgroup per 64 points the atomics on k sizes were half of the assignment's
+// time (n = 100000, k = 64: 52 us with them, 28 us without).
+struct AssignPart {
+    double J;
+    int64_t changed;
+};
+__device__ __forceinline__ AssignPart *assign_parts(const Inst &in) { return reinterpret_cast<AssignPart *>(in.perm); }
+__device__ __forceinline__ uint8_t *assign_sizes(const Inst &in, int32_t c) {
+    return reinterpret_cast<uint8_t *>(in.blk_hist + (int64_t)c * in.nblk);
+}
+__device__ __forceinline__ int64_t assign_blocks(const Inst &in) { return (in.n + kAssignPts - 1) / kAssignPts; }
+
+// ACROSS: the value was stored by another workgroup of the same launch.
+template <bool ACROSS, typename T> __device__ __forceinline__ T part_load(const T *p) {
+    if constexpr (ACROSS) return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    return *p;
+}
+template <bool ACROSS, typename T> __device__ __forceinline__ void part_store(T *p, T v) {
+    if constexpr (ACROSS) __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    else *p = v;
+}
+
+// J of the input labels and the number of changed labels, by the first 256
+// threads of a workgroup (all of its threads call).
+template <bool ACROSS>
+__device__ __forceinline__ void finish_objective(const Inst &in, double *wJ, long long *wC) {
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    if (tid < kPtsPerBlock) {
+        const AssignPart *part = assign_parts(in);
+        const int64_t nb = assign_blocks(in);
+        double J = 0.0;
+        long long changed = 0;
+        for (int64_t t = tid; t < nb; t += kPtsPerBlock) {
+            J += part_load<ACROSS>(&part[t].J);
+            changed += part_load<ACROSS>(&part[t].changed);
+        }
+        J = wave_sum(J);
+        changed = wave_sum(changed);
+        if (lane == 0) {
+            wJ[wave] = J;
+            wC[wave] = changed;
+        }
+    }
+    __syncthreads();
+    if (tid == 0) {
+        double tj = 0.0;
+        long long tc = 0;
+        for (int w = 0; w < kPtsPerBlock / kWave; ++w) {
+            tj += wJ[w];
+            tc += wC[w];
+        }
+        *in.J_in = tj;
+        *in.n_changed = tc;
+    }
+}
+
+// Size of cluster c, by LANES lanes of a wave (this one is `sub`); lane 0 of
+// them writes it.  The blocks' bytes are read four at a time, those past the
+// last block left out.
+template <bool ACROSS, int LANES>
+__device__ __forceinline__ void finish_size(const Inst &in, int32_t c, int sub) {
+    const uint32_t *row = reinterpret_cast<const uint32_t *>(assign_sizes(in, c));
+    const int64_t nb = assign_blocks(in);
+    uint32_t sum = 0;
+    for (int64_t t = sub; 4 * t < nb; t += LANES) {
+        const uint32_t w = part_load<ACROSS>(row + t);
+        const int64_t left = nb - 4 * t;
+        sum += (w & 0xFFu) + (left > 1 ? (w >> 8) & 0xFFu : 0u) + (left > 2 ? (w >> 16) & 0xFFu : 0u) +
+               (left > 3 ? w >> 24 : 0u);
+    }
+#pragma unroll
+    for (int off = LANES / 2; off > 0; off >>= 1) sum += __shfl_xor(sum, off, kWave);
+    if (sub == 0) in.counts_out[c] = (int32_t)sum;
+}
+
+// 64 points per workgroup, one per lane, the clusters dealt to the NW waves in
+// turn.  A thread per point summing every cluster's partials alone waited load
+// batch after load batch in n/256 workgroups; here a wave's chain is k / NW
+// clusters long, the next cluster's loads in flight (n = 3001, k = 12: 18 ->
+// 9.4 us with the norms and sums included; n = 60000, k = 10: 63 -> 18 us; n =
+// 100000, k = 64: 73 -> 29 us, 57 MB moved).  D's rows (a contiguous stretch of
+// 64 k floats) leave through LDS as whole lines when k <= 128.
+//
+// SMALL (one problem whose slots x strips of own-cluster sums are few): each
+// wave also computes the centroid norms of its clusters, and the last workgroup
+// to arrive adds up the parts, so neither takes a launch.  With few workgroups
+// the fence that orders the parts costs less than a launch; with hundreds it
+// does not.
+template <int NW, bool MULTI, bool SMALL>
+__global__ __launch_bounds__(NW *kWave) void assign_fused(InstSet s, const int32_t *labels_in_all,
+                                                          int32_t *labels_out_all, int stage_d) {
+    static_assert(kPtsPerBlock == 4 * kAssignPts && NW * kWave >= kPtsPerBlock, "four workgroups per label block");
+    extern __shared__ int32_t sh[];  // off[k+1], hist[k], ct[k], first[k], slots[k], D rows
+    __shared__ float wbest[NW][kAssignPts], wown[NW][kAssignPts];
+    __shared__ int32_t warg[NW][kAssignPts];
+    __shared__ double wJ[4];
+    __shared__ long long wC[4];
+    __shared__ int32_t last;
+    constexpr int NT = NW * kWave;
     Inst in;
     int64_t lb;
-    if (!locate<MULTI>(s, s.blk_start, blockIdx.x, in, lb)) return;
+    // the label blocks' grid, four workgroups to a block
+    if (!locate<MULTI>(s, s.blk_start, blockIdx.x >> 2, in, lb)) return;
+    lb = 4 * lb + (blockIdx.x & 3);
+    if (lb * kAssignPts >= in.n) return;  // uniform
     const int32_t k = in.k;
-    const int64_t L = in.L, ldp = in.ldp;
-    const float *__restrict__ P = in.P;
+    const int64_t ldp = in.ldp;
     const int32_t *__restrict__ labels_in = labels_in_all + in.lab_off;
     int32_t *__restrict__ labels_out = labels_out_all + in.lab_off;
     int32_t *off = sh;
     int32_t *hist = sh + (k + 1);
-    int32_t *seg = hist + k;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    float *ct = reinterpret_cast<float *>(hist + k);
+    int32_t *first = hist + 2 * k, *slots = hist + 3 * k;
+    float *dst = reinterpret_cast<float *>(hist + 4 * k);  // row stride odd: no bank conflicts
+    const int dld = k | 1;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
 
-    if (*in.err != 0) {
+    // what every point needs, loaded at once: a chain of dependent loads is most
+    // of this kernel's time when the problem is small
+    const int32_t bad = *in.err;
+    const int64_t i = lb * kAssignPts + lane;
+    const bool valid = i < in.n;
+    const float dii = in.diag[min(i, in.n - 1)];
+    const int32_t a_in = valid ? labels_in[i] : -1;
+    for (int c = tid; c <= k; c += NT) off[c] = in.offsets[c];
+    for (int c = tid; c < k; c += NT) {
+        hist[c] = 0;
+        if constexpr (!SMALL) ct[c] = in.ctilde[c];
+    }
+    if (bad != 0) {
         if (lb == 0 && tid == 0) {
             *in.n_changed = -1;
             *in.J_in = __builtin_nan("");
         }
         return;
     }
-    for (int c = tid; c <= k; c += kPtsPerBlock) off[c] = in.offsets[c];
-    for (int c = tid; c < k; c += kPtsPerBlock) hist[c] = 0;
+    __syncthreads();
+    // segment (q, c) of the sweep sits in slot q + c: cluster c has the slots of
+    // the chunks its positions lie in (positions and L fit 32 bits)
+    for (int c = tid; c < k; c += NT) {
+        const uint32_t lo = (uint32_t)off[c], hi = (uint32_t)off[c + 1], L = (uint32_t)in.L;
+        const uint32_t q0 = lo / L;
+        first[c] = (int32_t)q0 + c;
+        slots[c] = hi > lo ? (int32_t)((hi - 1) / L - q0) + 1 : 0;
+    }
     __syncthreads();
 
-    const int64_t i = lb * kPtsPerBlock + tid;
-    const bool valid = i < in.n;
-    const float dii = valid ? in.diag[i] : 0.f;
-    const int32_t a_in = valid ? labels_in[i] : -1;
-    float best = __builtin_inff();
+    float best = __builtin_inff(), own = 0.f;
     int32_t arg = -1;
-    float own = 0.f;
-    auto visit = [&](int32_t c, float dic) {
-        if (in.D_out) in.D_out[i * k + c] = dic;
-        if (c == a_in) own = dic;
-        if (dic < best) {
-            best = dic;
-            arg = c;
-        }
-    };
     const float empty_d = (in.empty_policy == KKM_EMPTY_ZERO_CENTROID) ? dii : __builtin_inff();
-    // S_ic of cluster `cur` is the compensated sum of its segments' partials, in
-    // CSR order; clusters without a segment are empty
-    int32_t cur = -1;
-    float sum = 0.f, comp = 0.f;
-    auto close = [&]() {
-        const float e = (sum + comp) / (float)(off[cur + 1] - off[cur]);
-        visit(cur, fmaf(-2.0f, e, dii) + in.ctilde[cur]);
+    const float *__restrict__ Pi = in.P + min(i, in.n - 1);
+    // the first eight partials of a cluster (or of none: c >= k)
+    struct Head {
+        int32_t s0, m, cnt;
+        float v[8];
     };
-    // Segment (q, c) of the sweep sits in slot q + c; slots rise with CSR
-    // position.  A window of the slot -> cluster map is built in LDS, then each
-    // thread reads its column of the window's partials eight loads at a time.
-    const int64_t nslot = (in.n + L - 1) / L + k;
-    for (int64_t s0 = 0; s0 < nslot; s0 += kSlotWindow) {
-        const int w = (int)min((int64_t)kSlotWindow, nslot - s0);
-        for (int t = tid; t < w; t += kPtsPerBlock) seg[t] = -1;
-        __syncthreads();
-        for (int c = tid; c < k; c += kPtsPerBlock) {
-            const int64_t lo = off[c], hi = off[c + 1];
-            if (hi > lo) {
-                const int64_t a = max(lo / L + c, s0), b = min((hi - 1) / L + c, s0 + w - 1);
-                for (int64_t t = a; t <= b; ++t) seg[t - s0] = c;
-            }
-        }
-        __syncthreads();
-        if (valid) {
-            for (int t0 = 0; t0 < w; t0 += 8) {
-                float v[8];
+    auto load8 = [&](const float *Ps, int32_t t0, int32_t m, float (&v)[8]) {
 #pragma unroll
-                for (int u = 0; u < 8; ++u) {
-                    const int32_t c = (t0 + u < w) ? seg[t0 + u] : -1;
-                    v[u] = (c >= 0) ? P[(s0 + t0 + u) * ldp + i] : 0.f;
-                }
+        for (int u = 0; u < 8; ++u) v[u] = (t0 + u < m) ? Ps[(t0 + u) * ldp] : 0.f;
+    };
+    auto head_of = [&](int32_t c, Head &h) {
+        h.s0 = c < k ? __builtin_amdgcn_readfirstlane(first[c]) : 0;
+        h.m = c < k ? __builtin_amdgcn_readfirstlane(slots[c]) : 0;
+        h.cnt = c < k ? __builtin_amdgcn_readfirstlane(off[c + 1] - off[c]) : 0;
+        load8(Pi + h.s0 * ldp, 0, h.m, h.v);
+    };
+    Head cur, ahead;
+    head_of(wave, cur);
+#pragma unroll 1
+    for (int32_t c = wave; c < k; c += NW) {
+        head_of(c + NW, ahead);  // the next cluster's loads wait with this one's
+        float dic = empty_d, norm = 0.f;
+        if (cur.m > 0) {
+            // S_ic: the compensated sum of the cluster's partials in CSR order
+            float sum = 0.f, comp = 0.f;
+            auto add = [&](const float (&v)[8]) {
 #pragma unroll
-                for (int u = 0; u < 8; ++u) {
-                    const int32_t c = (t0 + u < w) ? seg[t0 + u] : -1;
-                    if (c < 0) continue;
-                    if (c != cur) {
-                        if (cur >= 0) close();
-                        for (int32_t e = cur + 1; e < c; ++e) visit(e, empty_d);
-                        cur = c;
-                        sum = comp = 0.f;
-                    }
+                for (int u = 0; u < 8; ++u) {  // adding 0 past the last slot changes nothing
                     float x, er;
                     two_sum(sum, v[u], x, er);
                     sum = x;
                     comp += er;
                 }
+            };
+            if constexpr (SMALL)  // the cluster's slots follow each other
+                norm = __shfl(cluster_norm_wave(in.Zp + (int64_t)cur.s0 * in.nws, cur.m * (int32_t)in.nws,
+                                                cur.cnt, lane), 0, kWave);
+            else
+                norm = ct[c];
+            add(cur.v);
+            for (int32_t t0 = 8; t0 < cur.m; t0 += 8) {
+                float v[8];
+                load8(Pi + cur.s0 * ldp, t0, cur.m, v);
+                add(v);
+            }
+            dic = fmaf(-2.0f, (sum + comp) / (float)cur.cnt, dii) + norm;
+        }
+        if constexpr (SMALL)
+            if (lb == 0 && lane == 0 && in.ctilde_out) in.ctilde_out[c] = norm;
+        if (stage_d)
+            dst[lane * dld + c] = dic;
+        else if (in.D_out && valid)
+            in.D_out[i * k + c] = dic;
+        if (c == a_in) own = dic;
+        if (dic < best) {
+            best = dic;
+            arg = c;
+        }
+        cur = ahead;
+    }
+    wbest[wave][lane] = best;
+    warg[wave][lane] = arg;
+    wown[wave][lane] = own;  // 0 but in the wave of the point's own cluster
+    __syncthreads();
+    if (wave == 0) {
+        double own_d = 0.0;
+        long long changed = 0;
+        if (valid) {
+            for (int w = 1; w < NW; ++w) {
+                const float b = wbest[w][lane];
+                const int32_t a = warg[w][lane];
+                own += wown[w][lane];
+                if (b < best || (b == best && a >= 0 && a < arg)) {  // ties: the lowest index
+                    best = b;
+                    arg = a;
+                }
+            }
+            if (arg < 0) arg = a_in;
+            labels_out[i] = arg;
+            atomicAdd(&hist[arg], 1);
+            changed = (arg != a_in);
+            own_d = (double)own;
+        }
+        const double wj = wave_sum(own_d);
+        const long long wc = wave_sum(changed);
+        if (lane == 0) {
+            part_store<SMALL>(&assign_parts(in)[lb].J, wj);
+            part_store<SMALL>(&assign_parts(in)[lb].changed, (int64_t)wc);
+        }
+    }
+    if (stage_d) {
+        // element e of the block's rows is (e / k, e % k): stepped, not divided
+        const int total = (int)min((int64_t)kAssignPts, in.n - lb * kAssignPts) * k;
+        float *out = in.D_out + lb * kAssignPts * (int64_t)k;
+        const int dr = NT / k, dc = NT % k;
+        int r = tid / k, c = tid % k;
+        for (int e = tid; e < total; e += NT) {
+            out[e] = dst[r * dld + c];
+            r += dr;
+            c += dc;
+            if (c >= k) {
+                c -= k;
+                ++r;
             }
         }
-        __syncthreads();
-    }
-    double own_d = 0.0;
-    long long changed = 0;
-    if (valid) {
-        if (cur >= 0) close();
-        for (int32_t e = cur + 1; e < k; ++e) visit(e, empty_d);
-        if (arg < 0) arg = a_in;
-        labels_out[i] = arg;
-        atomicAdd(&hist[arg], 1);
-        changed = (arg != a_in);
-        own_d = (double)own;
-    }
-    // block reductions in a fixed order
-    const double wj = wave_sum(own_d);
-    const long long wc = wave_sum(changed);
-    if (lane == 0) {
-        wJ[wave] = wj;
-        wC[wave] = wc;
     }
     __syncthreads();
-    if (tid == 0) {
-        double bj = 0.0;
-        long long bc = 0;
-        for (int w = 0; w < kPtsPerBlock / kWave; ++w) {
-            bj += wJ[w];
-            bc += wC[w];
-        }
-        in.Jpart[lb] = bj;
-        if (bc) atomicAdd((unsigned long long *)in.n_changed, (unsigned long long)bc);
+    for (int c = tid; c < k; c += NT) part_store<SMALL>(assign_sizes(in, c) + lb, (uint8_t)hist[c]);
+    if constexpr (SMALL) {
+        __syncthreads();  // every part of this workgroup is stored before its arrival
+        if (tid == 0)
+            last = __hip_atomic_fetch_add(in.err + 1, 1, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT) ==
+                   (int32_t)assign_blocks(in) - 1;
+        __syncthreads();
+        if (!last) return;  // uniform
+        for (int32_t c = tid >> 4; c < k; c += NT / 16)  // 16 lanes read up to 64 blocks' sizes at once
+            finish_size<true, 16>(in, c, tid & 15);
+        finish_objective<true>(in, wJ, wC);
     }
-    for (int c = tid; c < k; c += kPtsPerBlock)
-        if (hist[c]) atomicAdd(&in.counts_out[c], hist[c]);
 }
 
-// J of the input labels: each problem's block partials summed in a fixed
-// order by one workgroup (a kernel of its own: a device-wide release fence
-// in every assignment workgroup costs far more than this launch).
+// The end of a step: one workgroup per (problem, cluster) adds the cluster's
+// size, cluster 0's also the objective and the changed count (a kernel of its
+// own: a device-wide release fence in every assignment workgroup of a large
+// problem costs far more than this launch).
 template <bool MULTI>
-__global__ __launch_bounds__(kPtsPerBlock) void j_finalize(InstSet s) {
+__global__ __launch_bounds__(kPtsPerBlock) void step_finish(InstSet s) {
     __shared__ double wJ[kPtsPerBlock / kWave];
+    __shared__ long long wC[kPtsPerBlock / kWave];
     Inst in;
-    if constexpr (MULTI) {
-        const int32_t b = blockIdx.x;
-        if (b >= s.count) return;
-        if (uniform_load(s.blk_start + b) >= uniform_load(s.blk_start + s.count)) return;
-        in = uniform_load(s.table + b);
-    } else {
-        in = s.one;
-    }
+    int64_t c;
+    if (!locate<MULTI>(s, s.cl_start, blockIdx.x, in, c)) return;
     if (*in.err != 0) return;  // the assignment has published NaN
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    double acc = 0.0;
-    for (int64_t t = tid; t < in.nblk; t += kPtsPerBlock) acc += in.Jpart[t];
-    const double ws = wave_sum(acc);
-    if (lane == 0) wJ[wave] = ws;
-    __syncthreads();
-    if (tid == 0) {
-        double tot = 0.0;
-        for (int w = 0; w < kPtsPerBlock / kWave; ++w) tot += wJ[w];
-        *in.J_in = tot;
-    }
+    if (threadIdx.x < kWave) finish_size<false, kWave>(in, (int32_t)c, threadIdx.x);
+    if (c == 0) finish_objective<false>(in, wJ, wC);
 }
 
 // Geometry shared by the workspace sizing and the kernels.
@@ -658,11 +1077,11 @@ void inst_carve(void *base, const InstGeom &g, Inst *in, size_t *bytes) {
     int32_t *counts = c.take<int32_t>((size_t)g.k);
     int32_t *blk_hist = c.take<int32_t>((size_t)g.k * (size_t)g.nblk);
     int32_t *blk_bad = c.take<int32_t>((size_t)g.nblk);
-    int32_t *err = c.take<int32_t>(1);
+    int32_t *err = c.take<int32_t>(2);  // bad labels; the assignment's arrival counter
     float *P = c.take<float>((size_t)g.slots * (size_t)g.ldp);
     float *Zp = c.take<float>((size_t)g.slots * (size_t)g.nws_max);
     float *ctilde = c.take<float>((size_t)g.k);
-    double *Jpart = c.take<double>((size_t)g.nblk);
+    (void)c.take<double>((size_t)g.nblk);
     if (bytes) *bytes = c.bytes();
     if (!in) return;
     in->n = g.n;
@@ -679,7 +1098,6 @@ void inst_carve(void *base, const InstGeom &g, Inst *in, size_t *bytes) {
     in->P = P;
     in->Zp = Zp;
     in->ctilde = ctilde;
-    in->Jpart = Jpart;
 }
 
 int64_t inst_sweep_items(const InstGeom &g, int32_t k_store) {
@@ -695,12 +1113,25 @@ void inst_set_store(Inst *in, int32_t k_store) {
 
 namespace {
 
+// One problem small enough for the one-workgroup CSR build (its labels wait in
+// registers, eight per thread; k bounds its LDS): 5 us at n = 3001 for the three
+// launches' 11 us and their gaps.
+bool small_csr(int64_t n, int32_t k) { return n <= kSmallPts && k <= 256; }
+
+// Centroid norms and J inside the assignment: every workgroup reads all the
+// own-cluster sums, so only while those are few.
+bool small_norms(const Inst &in) {
+    return small_csr(in.n, in.k) && ((in.n + in.L - 1) / in.L + in.k) * in.nws <= 4096;
+}
+
+// Chunks of at most 64 positions of a K small enough that the sweep's
+// workgroups do not fill the chip: the eight-wave sweep.
+bool small_sweep(const Inst &in) { return in.L <= kWave && in.n <= kSmallPts; }
+
 template <bool MULTI>
-kkm_status step_launch_t(const InstSet &s, int64_t total_blocks, int64_t total_clusters,
-                         int64_t sweep_grid, int32_t max_k, int32_t k_store, bool vec,
-                         const int32_t *labels_in, int32_t *labels_out, hipStream_t stream) {
+kkm_status csr_launch(const InstSet &s, int64_t total_blocks, int64_t total_clusters, int32_t max_k,
+                      const int32_t *labels_in, hipStream_t stream) {
     const dim3 pb(kPtsPerBlock);
-    const TimedSpan whole = timing_begin(TK_ITERATE, stream);
     hipLaunchKernelGGL(v_block_hist<MULTI>, dim3((unsigned)total_blocks), pb,
                        (size_t)(max_k + 1) * sizeof(int32_t), stream, s, labels_in);
     KKM_HIP(hipGetLastError());
@@ -709,32 +1140,90 @@ kkm_status step_launch_t(const InstSet &s, int64_t total_blocks, int64_t total_c
     hipLaunchKernelGGL(v_scatter<MULTI>, dim3((unsigned)total_blocks), pb,
                        (size_t)(max_k + 1 + 4 * max_k) * sizeof(int32_t), stream, s, labels_in);
     KKM_HIP(hipGetLastError());
-    const dim3 sg((unsigned)sweep_grid), sb(kSweepThreads);
+    return KKM_OK;
+}
+
+// V of one problem.
+kkm_status csr_one(const InstSet &s, const int32_t *labels_in, hipStream_t stream) {
+    const Inst &in = s.one;
+    if (!small_csr(in.n, in.k)) return csr_launch<false>(s, in.nblk, in.k, in.k, labels_in, stream);
+    hipLaunchKernelGGL(v_csr_small, dim3(1), dim3(kSmallThreads),
+                       (size_t)(1 + kSmallThreads / kWave) * in.k * sizeof(int32_t), stream, in,
+                       labels_in);
+    KKM_HIP(hipGetLastError());
+    return KKM_OK;
+}
+
+// Four waves cover up to 8 clusters in two rounds; sixteen take more, while the
+// workgroups are few: with many the chip is full either way and large workgroups
+// fill it worse (n = 100000, k = 64: 52 us with sixteen, 29 us with four; n =
+// 3001, k = 12: 9.4 us with sixteen).  The results do not depend on it.
+constexpr int64_t kAssignWide = 128;  // label blocks
+template <bool MULTI, bool SMALL>
+kkm_status assign_launch(const InstSet &s, int64_t total_blocks, int32_t max_k, const int32_t *labels_in,
+                         int32_t *labels_out, hipStream_t stream) {
+    const int stage_d = !MULTI && s.one.D_out && max_k <= kAssignStageK;
+    size_t lds = (size_t)(5 * max_k + 1) * sizeof(int32_t);
+    if (stage_d) lds += (size_t)kAssignPts * (max_k | 1) * sizeof(float);
+    const dim3 grid((unsigned)(4 * total_blocks));
+    if (max_k <= 8 || total_blocks > kAssignWide)
+        hipLaunchKernelGGL((assign_fused<4, MULTI, SMALL>), grid, dim3(4 * kWave), lds, stream, s, labels_in,
+                           labels_out, stage_d);
+    else
+        hipLaunchKernelGGL((assign_fused<16, MULTI, SMALL>), grid, dim3(16 * kWave), lds, stream, s, labels_in,
+                           labels_out, stage_d);
+    KKM_HIP(hipGetLastError());
+    return KKM_OK;
+}
+
+// Centroid norms, assignment and objective.
+template <bool MULTI>
+kkm_status finish_launch(const InstSet &s, int64_t total_blocks, int64_t total_clusters, int32_t max_k,
+                         const int32_t *labels_in, int32_t *labels_out, hipStream_t stream) {
+    if (!MULTI && small_norms(s.one))
+        return assign_launch<false, true>(s, total_blocks, max_k, labels_in, labels_out, stream);
+    hipLaunchKernelGGL(centroid_norms<MULTI>, dim3((unsigned)total_clusters), dim3(256), 0, stream, s);
+    KKM_HIP(hipGetLastError());
+    KKM_TRY((assign_launch<MULTI, false>(s, total_blocks, max_k, labels_in, labels_out, stream)));
+    hipLaunchKernelGGL(step_finish<MULTI>, dim3((unsigned)total_clusters), dim3(kPtsPerBlock), 0, stream, s);
+    KKM_HIP(hipGetLastError());
+    return KKM_OK;
+}
+
+template <bool MULTI>
+kkm_status step_launch_t(const InstSet &s, int64_t total_blocks, int64_t total_clusters,
+                         int64_t sweep_grid, int32_t max_k, int32_t k_store, bool vec,
+                         const int32_t *labels_in, int32_t *labels_out, hipStream_t stream) {
+    const TimedSpan whole = timing_begin(TK_ITERATE, stream);
+    if constexpr (MULTI)
+        KKM_TRY(csr_launch<true>(s, total_blocks, total_clusters, max_k, labels_in, stream));
+    else
+        KKM_TRY(csr_one(s, labels_in, stream));
     const TimedSpan span = timing_begin(TK_SWEEP, stream);
-    if (k_store == KKM_F32) {
-        if (vec)
-            hipLaunchKernelGGL((spmm_row_sweep<float, true, MULTI>), sg, sb, 0, stream, s, labels_in);
+    if (!MULTI && small_sweep(s.one)) {
+        const dim3 sg((unsigned)(s.one.nws * ((s.one.n + s.one.L - 1) / s.one.L))), sb(kSmallWaves * kWave);
+        if (k_store == KKM_F32 && vec)
+            hipLaunchKernelGGL((spmm_small_sweep<float, true>), sg, sb, 0, stream, s.one, labels_in);
+        else if (k_store == KKM_F32)
+            hipLaunchKernelGGL((spmm_small_sweep<float, false>), sg, sb, 0, stream, s.one, labels_in);
+        else if (vec)
+            hipLaunchKernelGGL((spmm_small_sweep<uint16_t, true>), sg, sb, 0, stream, s.one, labels_in);
         else
-            hipLaunchKernelGGL((spmm_row_sweep<float, false, MULTI>), sg, sb, 0, stream, s, labels_in);
+            hipLaunchKernelGGL((spmm_small_sweep<uint16_t, false>), sg, sb, 0, stream, s.one, labels_in);
     } else {
-        if (vec)
+        const dim3 sg((unsigned)sweep_grid), sb(kSweepThreads);
+        if (k_store == KKM_F32 && vec)
+            hipLaunchKernelGGL((spmm_row_sweep<float, true, MULTI>), sg, sb, 0, stream, s, labels_in);
+        else if (k_store == KKM_F32)
+            hipLaunchKernelGGL((spmm_row_sweep<float, false, MULTI>), sg, sb, 0, stream, s, labels_in);
+        else if (vec)
             hipLaunchKernelGGL((spmm_row_sweep<uint16_t, true, MULTI>), sg, sb, 0, stream, s, labels_in);
         else
             hipLaunchKernelGGL((spmm_row_sweep<uint16_t, false, MULTI>), sg, sb, 0, stream, s, labels_in);
     }
     KKM_HIP(hipGetLastError());
     timing_end(span, stream);
-    if (k_store == KKM_F32)
-        hipLaunchKernelGGL((centroid_norms<4, MULTI>), dim3((unsigned)total_clusters), dim3(256), 0, stream, s);
-    else
-        hipLaunchKernelGGL((centroid_norms<8, MULTI>), dim3((unsigned)total_clusters), dim3(256), 0, stream, s);
-    KKM_HIP(hipGetLastError());
-    hipLaunchKernelGGL(assign_fused<MULTI>, dim3((unsigned)total_blocks), pb,
-                       (size_t)(2 * max_k + 1 + kSlotWindow) * sizeof(int32_t), stream, s,
-                       labels_in, labels_out);
-    KKM_HIP(hipGetLastError());
-    hipLaunchKernelGGL(j_finalize<MULTI>, dim3(MULTI ? (unsigned)s.count : 1u), pb, 0, stream, s);
-    KKM_HIP(hipGetLastError());
+    KKM_TRY(finish_launch<MULTI>(s, total_blocks, total_clusters, max_k, labels_in, labels_out, stream));
     timing_end(whole, stream);
     return KKM_OK;
 }
@@ -763,26 +1252,10 @@ kkm_status step_launch_custom(const Inst &in, const int32_t *labels_in, int32_t 
     InstSet s{};
     s.count = 1;
     s.one = in;
-    const int32_t k = in.k;
-    const dim3 pb(kPtsPerBlock);
     const TimedSpan whole = timing_begin(TK_ITERATE, stream);
-    hipLaunchKernelGGL(v_block_hist<false>, dim3((unsigned)in.nblk), pb,
-                       (size_t)(k + 1) * sizeof(int32_t), stream, s, labels_in);
-    KKM_HIP(hipGetLastError());
-    hipLaunchKernelGGL(v_cluster_scan<false>, dim3((unsigned)k), dim3(256), 0, stream, s);
-    KKM_HIP(hipGetLastError());
-    hipLaunchKernelGGL(v_scatter<false>, dim3((unsigned)in.nblk), pb,
-                       (size_t)(k + 1 + 4 * k) * sizeof(int32_t), stream, s, labels_in);
-    KKM_HIP(hipGetLastError());
+    KKM_TRY(csr_one(s, labels_in, stream));
     KKM_TRY(sweep(stream));  // times its own launches
-    hipLaunchKernelGGL((centroid_norms<4, false>), dim3((unsigned)k), dim3(256), 0, stream, s);
-    KKM_HIP(hipGetLastError());
-    hipLaunchKernelGGL(assign_fused<false>, dim3((unsigned)in.nblk), pb,
-                       (size_t)(2 * k + 1 + kSlotWindow) * sizeof(int32_t), stream, s, labels_in,
-                       labels_out);
-    KKM_HIP(hipGetLastError());
-    hipLaunchKernelGGL(j_finalize<false>, dim3(1u), pb, 0, stream, s);
-    KKM_HIP(hipGetLastError());
+    KKM_TRY(finish_launch<false>(s, in.nblk, in.k, in.k, labels_in, labels_out, stream));
     timing_end(whole, stream);
     return KKM_OK;
 }
@@ -807,16 +1280,7 @@ kkm_status vcsr_build(const int32_t *labels, int64_t n, int32_t k, int32_t *blk_
     in.offsets = offsets;
     in.counts_out = counts_out;
     in.n_changed = n_changed;
-    const dim3 pb(kPtsPerBlock);
-    hipLaunchKernelGGL(v_block_hist<false>, dim3((unsigned)in.nblk), pb, (size_t)(k + 1) * sizeof(int32_t),
-                       stream, s, labels);
-    KKM_HIP(hipGetLastError());
-    hipLaunchKernelGGL(v_cluster_scan<false>, dim3((unsigned)k), dim3(256), 0, stream, s);
-    KKM_HIP(hipGetLastError());
-    hipLaunchKernelGGL(v_scatter<false>, dim3((unsigned)in.nblk), pb,
-                       (size_t)(k + 1 + 4 * k) * sizeof(int32_t), stream, s, labels);
-    KKM_HIP(hipGetLastError());
-    return KKM_OK;
+    return csr_launch<false>(s, in.nblk, k, k, labels, stream);
 }
 
 size_t iterate_workspace_bytes(int64_t n, int32_t k) {

@@ -278,3 +278,39 @@ def test_gram_shape_values(kkm):
     with pytest.raises(kkm.KKMError) as e:
         kkm.kkm_gram(Xd, kkm.GAUSS, 0.05, shape=7)
     assert e.value.status == -1
+
+
+# the step's routes by size: the one-workgroup CSR build and the eight-wave sweep
+# (up to 8192 points, 256 clusters), norms and sums inside the assignment (few
+# own-cluster sums), sixteen or four waves per assignment workgroup, D through LDS
+# up to k = 128; at the edges of each, with 16-byte rows and with rows of odd stride
+@pytest.mark.parametrize("n,k,pad", [(1, 1, 0), (64, 5, 0), (65, 64, 3), (255, 9, 1), (1023, 8, 0),
+                                     (1025, 128, 1), (1500, 129, 0), (2049, 256, 0),
+                                     (2049, 257, 0), (4097, 16, 3), (8192, 17, 0), (8193, 17, 0)])
+@pytest.mark.parametrize("bf16", [False, True])
+def test_step_routes(kkm, n, k, pad, bf16):
+    import torch
+    rng = np.random.default_rng(9000 + n + k)
+    A = rng.uniform(-1, 1, (n, n)).astype(np.float32)
+    A = torch.from_numpy(np.triu(A) + np.triu(A, 1).T)
+    K = (A.to(torch.bfloat16) if bf16 else A)
+    K_or = K.double().numpy()
+    ldk = (n + 7) // 8 * 8 + pad
+    Kd = torch.empty((n, ldk), dtype=K.dtype, device="cuda")[:, :n]
+    Kd.copy_(K)
+    diag = to_dev(np.diag(K_or).astype(np.float32))
+    labels = rng.integers(0, k, n).astype(np.int32)
+    if k > 4:
+        labels[labels == k // 2] = 0  # an empty cluster
+    for policy in (0, 1):
+        say("  step route", n, k, pad, bf16, policy)
+        orc = oracle.step(K_or, k, labels, policy)
+        lab, cnt, ch, J, D, C = kkm.kkm_iterate(Kd, diag, to_dev(labels), k, empty_policy=policy,
+                                                D_out=True, ctilde_out=True)
+        torch.cuda.synchronize()
+        compare_step(K_or, k, labels, orc, D.cpu().numpy(), lab.cpu().numpy(), cnt.cpu().numpy(),
+                     int(ch.item()), float(J.item()), C.cpu().numpy(), what="n %d k %d" % (n, k))
+    bad = labels.copy()
+    bad[n // 2] = k
+    r = kkm.kkm_iterate(Kd, diag, to_dev(bad), k)
+    assert int(r[2].item()) == -1
