@@ -1,8 +1,10 @@
-// MFMA products for the learned feature map: 64 x 64 output tile per 256-thread
-// workgroup, 4 waves as 2 x 2, each one 32 x 32 MFMA block; k staged in LDS in
-// slabs of 32 as FP32 and rounded to the operand type when the fragments are
-// built (bfloat16: round to nearest even; FP32: unchanged).
-#include "gemm.h"
+// MFMA products for the learned feature map.  FP32 (the loss and the Lloyd
+// assignment of few points): 64 x 64 output tile per 256-thread workgroup, 4
+// waves as 2 x 2, each one 32 x 32 MFMA block; k staged in LDS in slabs of 32.
+// BF16: the 32 x 32 tiles of gemm_small.h.  Large products of k-contiguous
+// operands take the wide tiles below, which round to the operand type
+// (bfloat16: round to nearest even) when the fragments are built.
+#include "gemm_small.h"
 
 namespace kkm {
 
@@ -10,18 +12,8 @@ namespace {
 
 constexpr int TM = 64, TK = 32, TLD = TK + 1;
 
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-
 __device__ __forceinline__ __bf16 to_bf16(float f) {
     return (__bf16)f;  // round to nearest even (one hardware conversion on gfx950)
-}
-
-__device__ __forceinline__ float gelu(float z) {
-    return 0.5f * z * (1.0f + erff(z * 0.70710678118654752f));
-}
-__device__ __forceinline__ float gelu_grad(float z) {
-    return 0.5f * (1.0f + erff(z * 0.70710678118654752f)) +
-           z * expf(-0.5f * z * z) * 0.39894228040143268f;
 }
 
 // Stage a 64 x 32 operand slab (rows r0.., k k0..) into LDS as [row][k].
@@ -48,8 +40,8 @@ __device__ __forceinline__ void stage(const float *P, int64_t ld, int64_t rows, 
     }
 }
 
-template <int OP, bool AK, bool BK>
-__global__ __launch_bounds__(256) void gemm_kernel(GemmArgs g, int epi) {
+template <bool AK, bool BK>
+__global__ __launch_bounds__(256) void gemm_f32(GemmArgs g, int epi) {
     __shared__ float As[TM][TLD], Bs[TM][TLD];
     __shared__ double red[4];
     const int64_t m0 = (int64_t)blockIdx.y * TM, n0 = (int64_t)blockIdx.x * TM;
@@ -67,24 +59,9 @@ __global__ __launch_bounds__(256) void gemm_kernel(GemmArgs g, int epi) {
         __syncthreads();
         const float *ra = As[wm * 32 + l32];
         const float *rb = Bs[wn * 32 + l32];
-        if (OP == GEMM_BF16) {
-            // lane half h supplies k = 8h .. 8h+7 of each 16-wide step (same for A and B)
 #pragma unroll
-            for (int s = 0; s < TK / 16; ++s) {
-                bf16x8 x, y;
-#pragma unroll
-                for (int v = 0; v < 8; ++v) {
-                    x[v] = to_bf16(ra[16 * s + 8 * half + v]);
-                    y[v] = to_bf16(rb[16 * s + 8 * half + v]);
-                }
-                acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x, y, acc, 0, 0, 0);
-            }
-        } else {
-#pragma unroll
-            for (int s = 0; s < TK / 2; ++s)
-                acc = __builtin_amdgcn_mfma_f32_32x32x2f32(ra[2 * s + half], rb[2 * s + half], acc,
-                                                           0, 0, 0);
-        }
+        for (int s = 0; s < TK / 2; ++s)
+            acc = __builtin_amdgcn_mfma_f32_32x32x2f32(ra[2 * s + half], rb[2 * s + half], acc, 0, 0, 0);
         __syncthreads();
     }
 
@@ -96,27 +73,12 @@ __global__ __launch_bounds__(256) void gemm_kernel(GemmArgs g, int epi) {
         const int64_t m = m0 + wm * 32 + 8 * (r >> 2) + 4 * half + (r & 3);
         if (m >= g.M || n >= g.N) continue;
         const float v = g.alpha * acc[r];
-        switch (epi) {
-        case EPI_STORE:
+        if (epi == EPI_STORE) {
             g.C[m * g.ldc + n] = v;
-            break;
-        case EPI_BIAS:
-            g.C[m * g.ldc + n] = v + g.bias[n];
-            break;
-        case EPI_BIAS_GELU: {
-            const float z = v + g.bias[n];
-            if (g.C) g.C[m * g.ldc + n] = z;
-            g.C2[m * g.ldc2 + n] = gelu(z);
-            break;
-        }
-        case EPI_GELU_BWD:
-            g.C[m * g.ldc + n] = v * gelu_grad(g.Zp[m * g.ldz + n]);
-            break;
-        default: {  // EPI_LOSS
+        } else {  // EPI_LOSS
             const float e = v - g.Kb[m * g.ldkb + n];
             g.C[m * g.ldc + n] = e;
             sq += (double)e * (double)e;
-        }
         }
     }
     if (epi == EPI_LOSS) {
@@ -295,6 +257,42 @@ bool gemm_wide_fits(bool ak, bool bk, GemmEpi epi, const GemmArgs &g) {
     return ak && bk && epi != EPI_LOSS && g.M >= 32 && g.N >= 256 && g.M * g.N >= (1 << 20);
 }
 
+template <bool AK, bool BK, int KS, int EPI>
+__global__ __launch_bounds__(SNT) void gemm_small(SmallGemm g) {
+    __shared__ __attribute__((aligned(16))) SmallLds lds;
+    small_tile<AK, BK, KS, EPI>(g, blockIdx.x, AdamArgs{}, lds);
+}
+
+template <bool AK, bool BK, int KS, int EPI>
+kkm_status gemm_small_launch(const SmallGemm &g, hipStream_t stream) {
+    hipLaunchKernelGGL((gemm_small<AK, BK, KS, EPI>), dim3((unsigned)small_tiles(g)), dim3(SNT), 0, stream, g);
+    KKM_HIP(hipGetLastError());
+    return KKM_OK;
+}
+
+// The BF16 forms the network uses (all with alpha = 1).
+kkm_status gemm_bf16_small(bool ak, bool bk, GemmEpi epi, const GemmArgs &g, hipStream_t stream) {
+    SmallGemm s = small_gemm(ak, bk, g.A, g.lda, g.B, g.ldb, g.M, g.N, g.K, g.C, g.ldc);
+    s.C2 = g.C2;
+    if (g.alpha == 1.0f && ak && bk && epi == EPI_BIAS_GELU && (!g.C || g.ldc == g.ldc2)) {
+        s.x = g.bias;
+        s.ldc = g.ldc2;
+        return gemm_small_launch<true, true, SK, SE_BIAS_GELU>(s, stream);
+    }
+    if (g.alpha == 1.0f && ak && bk && epi == EPI_BIAS) {
+        s.x = g.bias;
+        return gemm_small_launch<true, true, SK, SE_BIAS>(s, stream);
+    }
+    if (g.alpha == 1.0f && ak && !bk && epi == EPI_GELU_BWD && g.ldz == g.ldc) {
+        s.x = g.Zp;
+        return gemm_small_launch<true, false, SK, SE_GELU_BWD>(s, stream);
+    }
+    if (g.alpha == 1.0f && !ak && !bk && epi == EPI_STORE)
+        return gemm_small_launch<false, false, 256, SE_GRAD>(s, stream);
+    set_error("internal: BF16 product in a form no kernel takes");
+    return KKM_ERR_UNSUPPORTED;
+}
+
 }  // namespace
 
 kkm_status gemm_launch(GemmOp op, bool ak, bool bk, GemmEpi epi, const GemmArgs &g,
@@ -311,23 +309,17 @@ kkm_status gemm_launch(GemmOp op, bool ak, bool bk, GemmEpi epi, const GemmArgs 
         KKM_HIP(hipGetLastError());
         return KKM_OK;
     }
+    if (op == GEMM_BF16) return gemm_bf16_small(ak, bk, epi, g, stream);
     const dim3 grid((unsigned)((g.N + TM - 1) / TM), (unsigned)((g.M + TM - 1) / TM));
     const dim3 blk(256);
-    const int e = (int)epi;
-#define KKM_GEMM(OPV, AKV, BKV) \
-    hipLaunchKernelGGL((gemm_kernel<OPV, AKV, BKV>), grid, blk, 0, stream, g, e)
-    if (op == GEMM_BF16) {
-        if (ak && bk) KKM_GEMM(GEMM_BF16, true, true);
-        else if (ak && !bk) KKM_GEMM(GEMM_BF16, true, false);
-        else if (!ak && bk) KKM_GEMM(GEMM_BF16, false, true);
-        else KKM_GEMM(GEMM_BF16, false, false);
-    } else {
-        if (ak && bk) KKM_GEMM(GEMM_F32, true, true);
-        else if (ak && !bk) KKM_GEMM(GEMM_F32, true, false);
-        else if (!ak && bk) KKM_GEMM(GEMM_F32, false, true);
-        else KKM_GEMM(GEMM_F32, false, false);
+    if (ak && bk && (epi == EPI_STORE || epi == EPI_LOSS))
+        hipLaunchKernelGGL((gemm_f32<true, true>), grid, blk, 0, stream, g, (int)epi);
+    else if (ak && !bk && epi == EPI_STORE)
+        hipLaunchKernelGGL((gemm_f32<true, false>), grid, blk, 0, stream, g, (int)epi);
+    else {
+        set_error("internal: FP32 product in a form no kernel takes");
+        return KKM_ERR_UNSUPPORTED;
     }
-#undef KKM_GEMM
     KKM_HIP(hipGetLastError());
     return KKM_OK;
 }

@@ -9,6 +9,7 @@
 // the loss products (Phi Phi^T and its gradient) run in FP32.  Adam updates the
 // FP32 master weights.
 #include "gemm.h"
+#include "gram_tile.h"
 
 namespace kkm {
 
@@ -101,19 +102,27 @@ __global__ void gather_block(const float *K, int64_t ldk, const int32_t *idx, in
     for (int64_t c = threadIdx.x; c < B; c += blockDim.x) out[r * B + c] = K[src * ldk + idx[c]];
 }
 
-// Adam (bias-corrected); omb1 = 1 - beta1 and omb2 = 1 - beta2 are formed in
-// double on the host, c1 = 1 - beta1^t, c2 = 1 - beta2^t.
-__global__ void adam_update(float *p, float *mo, float *ve, const float *g, int64_t n, float lr,
-                            float b1, float b2, float omb1, float omb2, float eps, float c1,
-                            float c2) {
+__global__ void adam_update(float *p, float *mo, float *ve, const float *g, int64_t n, AdamArgs a) {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= n) return;
-    const float gi = g[i];
-    const float m = b1 * mo[i] + omb1 * gi;
-    const float v = b2 * ve[i] + omb2 * gi * gi;
-    mo[i] = m;
-    ve[i] = v;
-    p[i] -= lr * (m / c1) / (sqrtf(v / c2) + eps);
+    adam_one(p[i], mo[i], ve[i], g[i], a);
+}
+
+AdamArgs adam_args(int32_t t, double lr, double beta1, double beta2, double eps) {
+    AdamArgs a;
+    a.lr = (float)lr;
+    a.b1 = (float)beta1;
+    a.b2 = (float)beta2;
+    a.omb1 = (float)(1.0 - beta1);
+    a.omb2 = (float)(1.0 - beta2);
+    a.eps = (float)eps;
+    a.c1 = (float)(1.0 - pow(beta1, (double)t));
+    a.c2 = (float)(1.0 - pow(beta2, (double)t));
+    return a;
+}
+
+bool adam_ok(double lr, double beta1, double beta2, double eps) {
+    return lr > 0 && beta1 >= 0 && beta1 < 1 && beta2 >= 0 && beta2 < 1 && eps > 0;
 }
 
 __global__ void index_range_check(const int32_t *idx, int64_t count, int64_t m, int32_t *bad) {
@@ -141,15 +150,69 @@ TrainWs carve_train(void *base, const Dims &m, int64_t B, size_t *bytes) {
     w.XB = c.take<float>((size_t)(B * m.d));
     w.KB = c.take<float>((size_t)(B * B));
     w.grad = c.take<float>((size_t)m.count());
-    w.part = c.take<double>((size_t)gemm_tiles(B, B));
+    // one per 64 x 64 tile, or per 16 rows of a small batch
+    const int64_t np = gemm_tiles(B, B), small = (B + 15) / 16;
+    w.part = c.take<double>((size_t)(B <= kSmallBatch && small > np ? small : np));
     if (bytes) *bytes = c.bytes();
     return w;
+}
+
+// The arguments of a small batch's step (train.hip); KB in place, no update.
+TrainStep small_step(float *th, const Dims &m, const float *XB, int64_t ldx, float *KB, int64_t ldkb,
+                     int64_t B, const TrainWs &w, double *loss) {
+    TrainStep t{};
+    t.B = B;
+    t.d = m.d;
+    t.h1 = m.h1;
+    t.h2 = m.h2;
+    t.out = m.out;
+    t.oW1 = m.oW1();
+    t.ob1 = m.ob1();
+    t.oW2 = m.oW2();
+    t.ob2 = m.ob2();
+    t.oW3 = m.oW3();
+    t.ob3 = m.ob3();
+    t.th = th;
+    t.XB = XB;
+    t.ldx = ldx;
+    t.KB = KB;
+    t.ldkb = ldkb;
+    t.kern.kernel = -1;
+    t.Z1 = w.Z1;
+    t.H1 = w.H1;
+    t.Z2 = w.Z2;
+    t.H2 = w.H2;
+    t.Phi = w.Phi;
+    t.dPhi = w.dPhi;
+    t.dZ2 = w.dZ2;
+    t.dZ1 = w.dZ1;
+    t.part = w.part;
+    t.loss = loss;
+    return t;
+}
+
+kkm_status small_train_step(TrainStep t, float *am, float *av, int32_t step, double lr, double beta1,
+                            double beta2, double eps, hipStream_t s) {
+    if (!adam_ok(lr, beta1, beta2, eps)) {
+        set_error("kkm_mlp_adam: bad arguments");
+        return KKM_ERR_ARG;
+    }
+    t.am = am;
+    t.av = av;
+    const AdamArgs a = adam_args(step, lr, beta1, beta2, eps);
+    return train_step_small(t, &a, s);
 }
 
 // Loss and gradient for a batch already gathered into XB [B, ldx] / KB [B, ldkb].
 kkm_status loss_grad(const float *th, const Dims &m, const float *XB, int64_t ldx,
                      const float *KB, int64_t ldkb, int64_t B, const TrainWs &w, float *grad,
                      double *loss, hipStream_t s) {
+    if (B <= kSmallBatch) {
+        // parameters and KB are only read: no update, no kernel to compute
+        TrainStep t = small_step(const_cast<float *>(th), m, XB, ldx, const_cast<float *>(KB), ldkb, B, w, loss);
+        t.grad = grad;
+        return train_step_small(t, nullptr, s);
+    }
     KKM_TRY(forward_rows(th, m, XB, ldx, B, w.Z1, w.H1, w.Z2, w.H2, w.Phi, m.out, s));
     // G = Phi Phi^T - K_B and the sum of its squares
     GemmArgs g = gemm_args(w.Phi, m.out, w.Phi, m.out, B, B, m.out, w.G, B);
@@ -294,17 +357,14 @@ extern "C" kkm_status kkm_mlp_loss_grad(const float *params, int64_t d, int64_t 
 extern "C" kkm_status kkm_mlp_adam(float *params, float *adam_m, float *adam_v, const float *grad,
                                    int64_t count, int32_t t, double lr, double beta1,
                                    double beta2, double eps, void *stream) {
-    if (count < 1 || t < 1 || !params || !adam_m || !adam_v || !grad || !(lr > 0) ||
-        !(beta1 >= 0 && beta1 < 1) || !(beta2 >= 0 && beta2 < 1) || !(eps > 0)) {
+    if (count < 1 || t < 1 || !params || !adam_m || !adam_v || !grad ||
+        !adam_ok(lr, beta1, beta2, eps)) {
         set_error("kkm_mlp_adam: bad arguments");
         return KKM_ERR_ARG;
     }
-    const float c1 = (float)(1.0 - pow(beta1, (double)t));
-    const float c2 = (float)(1.0 - pow(beta2, (double)t));
     hipLaunchKernelGGL(adam_update, dim3((unsigned)((count + 255) / 256)), dim3(256), 0,
-                       (hipStream_t)stream, params, adam_m, adam_v, grad, count, (float)lr,
-                       (float)beta1, (float)beta2, (float)(1.0 - beta1), (float)(1.0 - beta2),
-                       (float)eps, c1, c2);
+                       (hipStream_t)stream, params, adam_m, adam_v, grad, count,
+                       adam_args(t, lr, beta1, beta2, eps));
     KKM_HIP(hipGetLastError());
     return KKM_OK;
 }
@@ -352,6 +412,11 @@ extern "C" kkm_status kkm_mlp_train(float *params, float *adam_m, float *adam_v,
         hipLaunchKernelGGL(gather_block, dim3((unsigned)B), dim3(256), 0, s, Ktrain, ldk, idx, B,
                            w.KB);
         KKM_HIP(hipGetLastError());
+        if (B <= kSmallBatch) {
+            TrainStep t = small_step(params, m, w.XB, d, w.KB, B, B, w, loss_trace + st);
+            KKM_TRY(small_train_step(t, adam_m, adam_v, t0 + st + 1, lr, beta1, beta2, eps, s));
+            continue;
+        }
         KKM_TRY(loss_grad(params, m, w.XB, d, w.KB, B, B, w, w.grad, loss_trace + st, s));
         KKM_TRY(kkm_mlp_adam(params, adam_m, adam_v, w.grad, m.count(), t0 + st + 1, lr, beta1,
                              beta2, eps, stream));
@@ -397,6 +462,12 @@ extern "C" kkm_status kkm_mlp_train_fresh(float *params, float *adam_m, float *a
     for (int32_t st = 0; st < steps; ++st) {
         // step st trains on rows st*B .. st*B+B-1 and their kernel values, computed now
         const float *XB = Xtrain + (int64_t)st * B * ldx;
+        if (B <= kSmallBatch) {
+            TrainStep t = small_step(params, m, XB, ldx, w.KB, B, B, w, loss_trace + st);
+            t.kern = BatchKernel{kernel_type, gt::epi_gamma(kernel_type, gamma), (float)coef0, degree};
+            KKM_TRY(small_train_step(t, adam_m, adam_v, t0 + st + 1, lr, beta1, beta2, eps, s));
+            continue;
+        }
         KKM_TRY(gram_launch(XB, B, d, ldx, kernel_type, gamma, coef0, degree, KKM_F32, KKM_F32,
                             w.KB, B, w.Z1 /* diag(K), unused */, gram_ws, gws, s));
         KKM_TRY(loss_grad(params, m, XB, ldx, w.KB, B, B, w, w.grad, loss_trace + st, s));
