@@ -455,12 +455,19 @@ extern "C" kkm_status kkm_fit_ex(const float *X, int64_t n, int64_t d, int64_t l
         }
         K = fb.K_own;
     }
-    const size_t gws = gram_workspace_bytes(n, d, gram_prec);
-    Carver c(nullptr);
-    c.take<char>(gws);
-    c.take<float>((size_t)n);   // diag
-    c.take<int32_t>(1);         // non-finite flag
-    KKM_HIP(hipMalloc(&fb.block, c.bytes()));
+    size_t gws = gram_workspace_bytes(n, d, gram_prec);
+    auto block_bytes = [&]() {
+        Carver c(nullptr);
+        c.take<char>(gws);
+        c.take<float>((size_t)n);  // diag
+        c.take<int32_t>(1);        // non-finite flag
+        return c.bytes();
+    };
+    if (hipMalloc(&fb.block, block_bytes()) != hipSuccess) {  // without the split it may fit
+        (void)hipGetLastError();
+        gws = gram_workspace_bytes(n, d, gram_prec, false);
+        KKM_HIP(hipMalloc(&fb.block, block_bytes()));
+    }
     Carver w(fb.block);
     void *gram_ws = w.take<char>(gws);
     float *diag = w.take<float>((size_t)n);

@@ -30,7 +30,7 @@
 
 #include <type_traits>
 
-#include "gram_tile.h"
+#include "gram_split.h"
 #include "iterate.h"
 
 namespace kkm {
@@ -50,12 +50,16 @@ struct RowSrc {
     int64_t ldx, d, dpad;
     unsigned char *Xq;  // [n][dpad] elements of the product's type, or null
     float *nrm, *scale;
+    unsigned char *Xs;  // FP32 product by split bfloat16, or null
+    int64_t groups;     // its row groups
+    int32_t *flag;
 };
 
 // Product view of one problem (only the member of its precision is used).
 struct GramSrc {
     F32Tile f;
     LowpTile q;
+    SplitTile s;  // in the place of f where Xs is set and its flag is not
 };
 
 // ---------------------------------------------------------------- 1. prologue
@@ -71,7 +75,16 @@ __global__ __launch_bounds__(256) void batch_prologue(const RowSrc *tab, const i
     const int64_t i = row - uniform_load(row_start + b);
     const int lane = threadIdx.x & 63;
     if constexpr (PREC == KKM_F32) {
-        sqnorm_row(r.X + i * r.ldx, r.d, r.nrm + i, lane);
+        const float *x = r.X + i * r.ldx;
+        sqnorm_row(x, r.d, r.nrm + i, lane);
+        if (r.Xs) {
+            // rows past n of the last group stay unwritten: they reach no output
+            const int rr = (int)(i % SPG);
+            unsigned char *dst = r.Xs + (i / SPG) * SPB + rr * 64;
+            for (int64_t c = lane; c < 4 * split_slabs(r.d); c += kWave)
+                split_chunk(x, r.d, 8 * c, true, dst + (c >> 2) * r.groups * SPB + (((c & 3) ^ ((rr >> 2) & 3)) * 16));
+            if (split_row_bad(x, r.d, lane) && lane == 0) atomicOr(r.flag, 1);
+        }
     } else {
         const int64_t eb = (PREC == KKM_BF16) ? 2 : 1;
         quantize_row<PREC>(r.X + i * r.ldx, r.d, r.dpad, r.Xq + i * r.dpad * eb, r.nrm + i,
@@ -80,6 +93,11 @@ __global__ __launch_bounds__(256) void batch_prologue(const RowSrc *tab, const i
 }
 
 // ---------------------------------------------------------------- 2. Gram
+
+union BatchF32Lds {
+    F32Lds f;
+    SplitLds s;
+};
 
 // Persistent: every workgroup pops chunks of kQueueChunk tiles until the
 // counter passes the tile total, so every wave reaches the exit.  Two
@@ -90,7 +108,7 @@ __global__ __launch_bounds__(GTHREADS, 2) void batch_gram(const GramSrc *tab,
                                                           const int64_t *tile_start,
                                                           int32_t count,
                                                           unsigned long long *queue) {
-    __shared__ __attribute__((aligned(16))) std::conditional_t<PREC == KKM_F32, F32Lds, LowpLds<true>> lds;
+    __shared__ __attribute__((aligned(1024))) std::conditional_t<PREC == KKM_F32, BatchF32Lds, LowpLds<true>> lds;
     __shared__ long long next;
     const int64_t total = uniform_load(tile_start + count);
     for (;;) {
@@ -104,9 +122,13 @@ __global__ __launch_bounds__(GTHREADS, 2) void batch_gram(const GramSrc *tab,
             const int32_t b = find_inst(tile_start, count, t);
             int64_t bi, bj;
             tile_coords(t - uniform_load(tile_start + b), bi, bj);
-            if constexpr (PREC == KKM_F32)
-                f32_tile<OUT>(uniform_load(&tab[b].f), bi, bj, lds);
-            else
+            if constexpr (PREC == KKM_F32) {
+                const SplitTile x = uniform_load(&tab[b].s);
+                if (x.Xs && uniform_load(x.flag) == 0)
+                    split_tile<OUT>(x, uniform_load(&tab[b].f.e), bi, bj, lds.s);
+                else
+                    f32_tile<OUT>(uniform_load(&tab[b].f), bi, bj, lds.f);
+            } else
                 lowp_tile<PREC, OUT>(uniform_load(&tab[b].q), bi, bj, lds);
         }
     }
@@ -254,6 +276,7 @@ struct Plan {
     int64_t *tile_start = nullptr, *row_start = nullptr;
     int32_t *status = nullptr, *iters = nullptr, *step = nullptr, *n_live = nullptr;
     int32_t *flag = nullptr;
+    int32_t *split_flags = nullptr;  // per problem: outside the split product's range
     double *objective = nullptr, *J = nullptr;
     int64_t *n_changed = nullptr;
     unsigned long long *queue = nullptr;
@@ -306,7 +329,7 @@ kkm_status check_instances(const kkm_instance *inst, int32_t count, int32_t gram
 // Lays the workspace out (sizes only when base == nullptr) and, with a base,
 // fills the host tables whose pointers refer to it.
 void make_plan(const kkm_instance *inst, int32_t count, int32_t gram_prec, int32_t k_store,
-               int32_t empty_policy, void *base, Plan &p) {
+               int32_t empty_policy, void *base, Plan &p, bool split = true) {
     p.count = count;
     Carver c(base);
     const size_t es = elem_bytes(k_store);
@@ -357,6 +380,15 @@ void make_plan(const kkm_instance *inst, int32_t count, int32_t gram_prec, int32
     p.n_live = c.take<int32_t>(1);
     p.flag = c.take<int32_t>(1);
     p.queue = c.take<unsigned long long>(1);
+    // FP32 products that the single run splits: last, so that a workspace
+    // without room for them serves the rest
+    p.split_flags = nullptr;
+    std::vector<unsigned char *> Xs(count, nullptr);
+    if (split && gram_prec == KKM_F32 && (reinterpret_cast<uintptr_t>(base) & 15) == 0) {
+        p.split_flags = c.take<int32_t>((size_t)count);
+        for (int32_t b = 0; b < count; ++b)
+            if (split_pays(inst[b].n, inst[b].d)) Xs[b] = c.take<unsigned char>(split_bytes(inst[b].n, inst[b].d));
+    }
     p.bytes = c.bytes();
 
     p.total_blocks = p.total_clusters = p.total_items = 0;
@@ -413,6 +445,9 @@ void make_plan(const kkm_instance *inst, int32_t count, int32_t gram_prec, int32
         r.Xq = Xq[b];
         r.nrm = nrm + row_off[b];
         r.scale = scale + row_off[b];
+        r.Xs = Xs[b];
+        r.groups = split_groups(q.n);
+        r.flag = p.split_flags ? p.split_flags + b : nullptr;
     }
     for (int32_t rnk = 0; rnk < count; ++rnk) {
         const int32_t b = order[rnk];
@@ -438,6 +473,7 @@ void make_plan(const kkm_instance *inst, int32_t count, int32_t gram_prec, int32
         g.f.ldx = q.ldx;
         g.f.vec_x = ((q.ldx % 4) == 0) && ((reinterpret_cast<uintptr_t>(q.X) & 15) == 0);
         g.f.e = e;
+        g.s = SplitTile{Xs[b], split_groups(q.n) * SPB, split_slabs(q.d), p.h_rtab[b].flag};
         g.q.Xq = Xq[b];
         g.q.ldq_bytes = p.h_rtab[b].dpad * eb;
         g.q.nslab = g.q.ldq_bytes / SLAB;
@@ -470,6 +506,7 @@ struct BatchBuffers {
 
 kkm_status launch_prologue(const Plan &p, int32_t gram_prec, hipStream_t s) {
     const dim3 g((unsigned)((p.total_n + 3) / 4)), b(256);
+    if (p.split_flags) fill_i32(p.split_flags, p.count, 0, s);
     if (gram_prec == KKM_F32)
         hipLaunchKernelGGL(batch_prologue<KKM_F32>, g, b, 0, s, p.rtab, p.row_start, p.count);
     else if (gram_prec == KKM_BF16)
@@ -551,6 +588,13 @@ extern "C" kkm_status kkm_fit_batched(const kkm_instance *inst, int32_t count, i
     }
     BatchBuffers bb;
     bb.stream = s;
+    // a workspace without room for the split (or not aligned for it) serves the
+    // FP32 product
+    bool split = true;
+    if (ws && (ws_bytes < p.bytes || (reinterpret_cast<uintptr_t>(ws) & 15) != 0)) {
+        split = false;
+        make_plan(inst, count, gram_prec, k_store, empty_policy, nullptr, p, split);
+    }
     if (ws) {
         if (ws_bytes < p.bytes) {
             set_error("kkm_fit_batched: workspace of %zu bytes is smaller than %zu", ws_bytes,
@@ -558,7 +602,13 @@ extern "C" kkm_status kkm_fit_batched(const kkm_instance *inst, int32_t count, i
             return KKM_ERR_NOMEM;
         }
     } else {
-        const hipError_t e = hipMalloc(&bb.ws_own, p.bytes);
+        hipError_t e = hipMalloc(&bb.ws_own, p.bytes);
+        if (e != hipSuccess && gram_prec == KKM_F32) {  // without the split it may fit
+            (void)hipGetLastError();
+            split = false;
+            make_plan(inst, count, gram_prec, k_store, empty_policy, nullptr, p, split);
+            e = hipMalloc(&bb.ws_own, p.bytes);
+        }
         if (e != hipSuccess) {
             set_error("kkm_fit_batched: cannot allocate %zu bytes (%s)", p.bytes,
                       hipGetErrorString(e));
@@ -566,7 +616,7 @@ extern "C" kkm_status kkm_fit_batched(const kkm_instance *inst, int32_t count, i
         }
         ws = bb.ws_own;
     }
-    make_plan(inst, count, gram_prec, k_store, empty_policy, ws, p);
+    make_plan(inst, count, gram_prec, k_store, empty_policy, ws, p, split);
 
     int dev = 0, cus = 0;
     KKM_HIP(hipGetDevice(&dev));

@@ -13,7 +13,8 @@
 // exactly symmetric.  B never reaches memory.
 //
 // Arithmetic of the product (gram_prec):
-//   F32   FP32 inputs, v_mfma_f32_32x32x2_f32.
+//   F32   FP32 inputs, v_mfma_f32_32x32x2_f32, or each input as three
+//         bfloat16 parts and six v_mfma_f32_32x32x16_bf16 (gram_split.h).
 //   BF16  inputs rounded to bfloat16 (round to nearest even), FP32 accumulation,
 //         v_mfma_f32_32x32x16_bf16.
 //   FP8   each row scaled by s_i = max_l |x_il| / 448 and rounded to OCP FP8
@@ -64,9 +65,13 @@ int group_log2(int64_t d, int32_t gram_prec) {
 
 }  // namespace
 
-size_t gram_workspace_bytes(int64_t n, int64_t d, int32_t gram_prec) {
+size_t gram_workspace_bytes(int64_t n, int64_t d, int32_t gram_prec, bool split) {
     Carver c(nullptr);
     c.take<float>((size_t)n);  // squared norms
+    if (gram_prec == KKM_F32 && split && split_pays(n, d)) {
+        c.take<int32_t>(1);  // flag: values left to the FP32 kernel
+        c.take<unsigned char>(split_bytes(n, d));
+    }
     if (gram_prec != KKM_F32) {
         c.take<float>((size_t)n);  // row scales
         const size_t eb = (gram_prec == KKM_BF16) ? 2 : 1;
@@ -79,7 +84,15 @@ kkm_status gram_launch(const float *X, int64_t n, int64_t d, int64_t ldx, int32_
                        double gamma, double coef0, int32_t degree, int32_t gram_prec,
                        int32_t k_store, void *K, int64_t ldk, float *diagK, void *ws,
                        size_t ws_bytes, hipStream_t stream, int32_t shape, bool packed) {
-    const size_t need = gram_workspace_bytes(n, d, gram_prec);
+    const bool full = (shape == KKM_GRAM_FULL);
+    Carver c(ws);
+    float *nrm = c.take<float>((size_t)n);
+    // a workspace without room for the split (or not aligned for it) is
+    // enough for the FP32 kernel
+    const size_t all = gram_workspace_bytes(n, d, gram_prec);
+    const bool split = gram_prec == KKM_F32 && split_pays(n, d) && ws_bytes >= all &&
+                       (reinterpret_cast<uintptr_t>(ws) & 15) == 0;
+    const size_t need = split ? all : gram_workspace_bytes(n, d, gram_prec, false);
     if (ws == nullptr || ws_bytes < need) {
         set_error("kkm_gram: workspace of %zu bytes is smaller than %zu", ws_bytes, need);
         return KKM_ERR_NOMEM;
@@ -89,8 +102,6 @@ kkm_status gram_launch(const float *X, int64_t n, int64_t d, int64_t ldx, int32_
                   (long long)d);
         return KKM_ERR_UNSUPPORTED;
     }
-    Carver c(ws);
-    float *nrm = c.take<float>((size_t)n);
     Epi e;
     e.n = n;
     e.ldk = ldk;
@@ -117,7 +128,6 @@ kkm_status gram_launch(const float *X, int64_t n, int64_t d, int64_t ldx, int32_
             return KKM_ERR_UNSUPPORTED;
         }
     }
-    const bool full = (shape == KKM_GRAM_FULL);
     // 256 x 256 tiles only on request: measured slower on MI355X at every n and
     // d tried (one workgroup per CU leaves the epilogue and the operand-load
     // latency of a tile without another tile to hide behind)
@@ -131,7 +141,7 @@ kkm_status gram_launch(const float *X, int64_t n, int64_t d, int64_t ldx, int32_
     const unsigned qgrid = (unsigned)((n + 3) / 4);
 
     if (gram_prec == KKM_F32) {
-        if (kernel == KKM_GAUSS) {
+        if (kernel == KKM_GAUSS && !split) {
             hipLaunchKernelGGL(row_sqnorms, dim3(qgrid), dim3(256), 0, stream, X, n, d, ldx, nrm);
             KKM_HIP(hipGetLastError());
         }
@@ -141,6 +151,11 @@ kkm_status gram_launch(const float *X, int64_t n, int64_t d, int64_t ldx, int32_
         a.ldx = ldx;
         a.vec_x = ((ldx % 4) == 0) && ((reinterpret_cast<uintptr_t>(X) & 15) == 0);
         a.e = e;
+        if (split) {
+            int32_t *flag = c.take<int32_t>(1);
+            unsigned char *Xs = c.take<unsigned char>(split_bytes(n, d));
+            return launch_gram_split(k_store, full, a, order, Xs, nrm, flag, stream);
+        }
         const TimedSpan span = timing_begin(TK_GRAM, stream);
         launch_gram_f32(k_store, full, dim3((unsigned)grid), a, order, stream);
         KKM_HIP(hipGetLastError());

@@ -1,0 +1,204 @@
+// The FP32 product of the kernel matrix on the bfloat16 matrix units: every
+// FP32 value is the sum of three bfloat16 values, x = h + m + l (each the
+// rounding of what the ones before left; the remainder is below 2^-26 |x|), and
+//   x y = (h h' + (h m' + m h') + (m m' + h l' + l h')) + terms below 2^-25 |x y|
+// so six v_mfma_f32_32x32x16_bf16, their products exact and their sums FP32,
+// take the place of eight v_mfma_f32_32x32x2_f32 at a sixteenth of their cost
+// each (2.5 PFLOP/s against 157 TFLOP/s).  A sum is rounded six times per 16
+// features instead of sixteen times, and the error against 64 bits is smaller
+// (X X^T of normal points, n = 16384, relative in norm: d = 16 3.4e-8 where the
+// FP32 kernel has 7.3e-8, d = 128 8.1e-8 / 2.0e-7, d = 784 1.2e-7 / 5.0e-7).
+//
+// n = 60000, d = 784: 25.8 -> 15.8 ms, 1.07 PFLOP/s of bfloat16 products, the
+// rate that a plain bfloat16 product of 8192^3 reaches on this card (1.13).
+//
+// Values whose low parts would leave the bfloat16 range, and infinities and
+// NaNs (inf - inf inside a split), are left to the FP32 kernel: the prologue
+// raises a flag on the device, this kernel then returns at once and the FP32
+// kernel, launched behind it, does the work; without the flag that one returns.
+//
+// Per 32-feature slab a 128 x 128 tile stages 2 x 24 KiB with direct
+// global-to-LDS loads, already in LDS order (the prologue wrote them so), single
+// buffered: three workgroups per CU hide each other's loads, as in the BF16
+// product.  A fragment feeds 6/3 as many MFMAs as there, so LDS is no bound.
+// Shared by the single- and many-instance Gram kernels.  Internal to the library.
+#pragma once
+
+#include "gram_tile.h"
+
+namespace kkm {
+namespace gt {
+
+namespace {
+
+// Rows are grouped by 16; a slab of 32 features of a group is three planes (h,
+// m, l) of 16 x 64 bytes.  16-byte chunk c of row r sits at chunk position
+// c ^ (r / 4 % 4), which spreads the fragment reads of 16 rows over all banks.
+constexpr int SPG = 16;                       // rows per group
+constexpr int SPK = 32;                       // features per slab
+constexpr int SPP = SPG * SPK * 2;            // bytes of one plane of a group
+constexpr int SPB = 3 * SPP;                  // bytes of a group's slab
+constexpr int SPT = GM / SPG * SPB;           // bytes of a tile operand's slab
+
+struct SplitLds {
+    unsigned char op[2][SPT];
+    float rn[2 * GM], rs[2 * GM];
+};
+
+// A matrix split and laid out: Xs [slab][group][plane][16 rows x 64 bytes].
+struct SplitTile {
+    const unsigned char *Xs;  // null: not split
+    int64_t slab_bytes;       // groups * SPB
+    int64_t nslab;
+    const int32_t *flag;      // set: a value is outside the split's range
+};
+
+__host__ __device__ inline int64_t split_groups(int64_t n) { return (n + GM - 1) / GM * (GM / SPG); }
+__host__ __device__ inline int64_t split_slabs(int64_t d) { return (d + SPK - 1) / SPK; }
+
+// The three parts of features k0 .. k0+7 of a row x (zeros past d, or all
+// zeros if !in), 16 bytes each, SPP apart.
+__device__ __forceinline__ void split_chunk(const float *x, int64_t d, int64_t k0, bool in, unsigned char *dst) {
+    bf16x8 h, m, l;
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+        const float a = x[min(k0 + u, d - 1)];
+        const float v = (in && k0 + u < d) ? a : 0.f;
+        h[u] = (__bf16)v;
+        const float v1 = v - (float)h[u];
+        m[u] = (__bf16)v1;
+        l[u] = (__bf16)(v1 - (float)m[u]);
+    }
+    *reinterpret_cast<bf16x8 *>(dst) = h;
+    *reinterpret_cast<bf16x8 *>(dst + SPP) = m;
+    *reinterpret_cast<bf16x8 *>(dst + 2 * SPP) = l;
+}
+
+// Whether a row (one whole wave) has a value outside the split's range: not
+// finite or above 2^60, or all of a row that is not zero below 2^-40.  Within
+// it no part that counts is subnormal.
+__device__ __forceinline__ bool split_row_bad(const float *x, int64_t d, int lane) {
+    float big = 0.f;
+    bool bad = false;
+    for (int64_t k = lane; k < d; k += kWave) {
+        const float v = fabsf(x[k]);
+        bad |= !(v <= 0x1p60f);
+        big = fmaxf(big, v);
+    }
+    big = wave_max(big);
+    return __ballot(bad) != 0 || (big > 0.f && big < 0x1p-40f);
+}
+
+// One 128 x 128 tile (bi, bj) and its epilogue.  FULL: tiles below the diagonal
+// swap the order of mixed terms, so they round as their mirror above does.
+template <typename OUT, bool FULL = false>
+__device__ __forceinline__ void split_tile(const SplitTile &x, const Epi &e, int64_t bi, int64_t bj, SplitLds &lds) {
+    const int64_t m0 = bi * GM, n0 = bj * GM;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wr = wave >> 1, wc = wave & 1;
+    const int half = lane >> 5, l32 = lane & 31;
+
+    // each wave copies a quarter of both operands' slabs, 1 KiB at a time
+    constexpr int Q = SPT / 4, NB = Q / 1024;
+    const unsigned char *ga = x.Xs + bi * SPT + wave * Q + lane * 16;
+    const unsigned char *gb = x.Xs + bj * SPT + wave * Q + lane * 16;
+    typedef __attribute__((address_space(3))) void lds_void;
+    typedef const __attribute__((address_space(1))) void glb_void;
+    auto fetch = [&]() {
+#pragma unroll
+        for (int b = 0; b < NB; ++b)
+            __builtin_amdgcn_global_load_lds((glb_void *)(ga + b * 1024), (lds_void *)(&lds.op[0][wave * Q + b * 1024]),
+                                             16, 0, 0);
+#pragma unroll
+        for (int b = 0; b < NB; ++b)
+            __builtin_amdgcn_global_load_lds((glb_void *)(gb + b * 1024), (lds_void *)(&lds.op[1][wave * Q + b * 1024]),
+                                             16, 0, 0);
+        ga += x.slab_bytes;
+        gb += x.slab_bytes;
+    };
+
+    f32x16 acc[2][2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+
+    stage_norms(e, m0, n0, lds.rn, lds.rs);
+    // lane half h of MFMA s takes the 8 features of chunk 2s + h of its row
+    const int swz = (l32 >> 2) & 3;
+    const int frag = (l32 >> 4) * SPB + (l32 & 15) * 64;
+    const unsigned char *As = lds.op[0] + wr * (4 * SPB) + frag, *Bs = lds.op[1] + wc * (4 * SPB) + frag;
+    for (int64_t kt = 0; kt < x.nslab; ++kt) {
+        fetch();
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        __syncthreads();
+        const int chunk[2] = {(half ^ swz) * 16, ((2 + half) ^ swz) * 16};
+        bf16x8 b[2][2][3];  // [s][ni][plane]
+#pragma unroll
+        for (int s = 0; s < 2; ++s)
+#pragma unroll
+            for (int i = 0; i < 2; ++i)
+#pragma unroll
+                for (int p = 0; p < 3; ++p)
+                    b[s][i][p] = *reinterpret_cast<const bf16x8 *>(Bs + i * (2 * SPB) + p * SPP + chunk[s]);
+        // A slab's 32 features are summed from zero and then added to the
+        // running sum: the matrix unit's own additions to a long sum cost more
+        // than the FP32 chain's at d = 784 (largest error of X X^T 1.4e-6 of its
+        // largest value against 1.3e-6; so 2.5e-7, for 4% of the time)
+#pragma unroll
+        for (int mi = 0; mi < 2; ++mi) {
+            f32x16 t[2];
+#pragma unroll
+            for (int ni = 0; ni < 2; ++ni)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) t[ni][r] = 0.f;
+#pragma unroll
+            for (int s = 0; s < 2; ++s) {
+                bf16x8 a[3];
+#pragma unroll
+                for (int p = 0; p < 3; ++p)
+                    a[p] = *reinterpret_cast<const bf16x8 *>(As + mi * (2 * SPB) + p * SPP + chunk[s]);
+                auto product = [&](int p, int q) {
+#pragma unroll
+                    for (int ni = 0; ni < 2; ++ni)
+                        t[ni] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[p], b[s][ni][q], t[ni], 0, 0, 0);
+                };
+                if (FULL && bi > bj) {
+                    product(2, 0);
+                    product(0, 2);
+                    product(1, 1);
+                    product(1, 0);
+                    product(0, 1);
+                    product(0, 0);
+                } else {
+                    product(0, 2);  // the small terms first
+                    product(2, 0);
+                    product(1, 1);
+                    product(0, 1);
+                    product(1, 0);
+                    product(0, 0);
+                }
+            }
+#pragma unroll
+            for (int ni = 0; ni < 2; ++ni)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) acc[mi][ni][r] += t[ni][r];
+        }
+        __syncthreads();  // every read of the slab is done
+    }
+    static_assert(sizeof(lds.op) >= epi_lds_bytes(2), "epilogue tile does not fit");
+    static_assert(sizeof(lds.op) >= epi_lds_bytes_bf16, "bfloat16 epilogue tile does not fit");
+    float *T = reinterpret_cast<float *>(&lds.op[0][0]);
+    if (FULL && bi != bj)
+        epilogue<OUT, true, 2>(e, acc, m0, n0, false, wr, wc, lane, T, lds.rn, lds.rs);
+    else
+        epilogue<OUT, false, 2>(e, acc, m0, n0, bi == bj, wr, wc, lane, T, lds.rn, lds.rs);
+}
+
+}  // namespace
+
+}  // namespace gt
+}  // namespace kkm

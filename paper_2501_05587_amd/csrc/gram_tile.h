@@ -610,8 +610,7 @@ inline TileOrder tile_order(int64_t n, int lg, bool full = false, int tile = GM)
     return o;
 }
 
-__device__ __forceinline__ bool tile_of_block(const TileOrder &o, int64_t &bi, int64_t &bj) {
-    const int64_t pid = blockIdx.x;
+__device__ __forceinline__ bool tile_of_block(const TileOrder &o, int64_t pid, int64_t &bi, int64_t &bj) {
     const int64_t t = (pid % 8) * o.per_xcd + pid / 8;
     if (t >= o.npos) return false;
     int64_t I, J;
@@ -630,6 +629,10 @@ __device__ __forceinline__ bool tile_of_block(const TileOrder &o, int64_t &bi, i
     bi = (I << o.lg) + (w & g1);
     bj = (J << o.lg) + (w >> o.lg);
     return bi <= bj && bj < o.nb;
+}
+
+__device__ __forceinline__ bool tile_of_block(const TileOrder &o, int64_t &bi, int64_t &bj) {
+    return tile_of_block(o, blockIdx.x, bi, bj);
 }
 
 // ---------------------------------------------------------------- FP32 product
@@ -1135,6 +1138,17 @@ __device__ __forceinline__ void quantize_row(const float *x, int64_t d, int64_t 
 // gram_lowp.hip, gram_lowp256.hip); g is the grid of the launch order.
 void launch_gram_f32(int32_t k_store, bool full, dim3 g, const F32Tile &a, const TileOrder &order,
                      hipStream_t stream);
+// The same where *flag is set, nothing else (a fixed number of workgroups walks
+// the tiles).
+void launch_gram_f32_flagged(int32_t k_store, bool full, const F32Tile &a, const TileOrder &order,
+                             const int32_t *flag, hipStream_t stream);
+// The FP32 product by split bfloat16 (gram_split.h): which products take it,
+// the bytes of the split matrix (16-byte aligned), and prologue, product and
+// the flagged FP32 kernel.
+bool split_pays(int64_t n, int64_t d);
+size_t split_bytes(int64_t n, int64_t d);
+kkm_status launch_gram_split(int32_t k_store, bool full, const F32Tile &a, const TileOrder &order,
+                             unsigned char *Xs, float *nrm, int32_t *flag, hipStream_t stream);
 void launch_gram_lowp(int32_t gram_prec, int32_t k_store, bool full, dim3 g, const LowpTile &a,
                       const TileOrder &order, hipStream_t stream);
 void launch_gram_lowp256(int32_t gram_prec, int32_t k_store, dim3 g, const LowpTile &a,

@@ -714,7 +714,7 @@ extern "C" kkm_status kkm_fit_packed(const float *X, int64_t n, int64_t d, int64
         return KKM_ERR_ARG;
     }
     hipStream_t s = (hipStream_t)stream;
-    const size_t gws = gram_workspace_bytes(n, d, gram_prec);
+    size_t gws = gram_workspace_bytes(n, d, gram_prec);
     void *block = nullptr, *K_own = nullptr;
     int32_t *hflag = nullptr;
     struct Guard {
@@ -737,11 +737,18 @@ extern "C" kkm_status kkm_fit_packed(const float *X, int64_t n, int64_t d, int64
         }
         K = K_own;
     }
-    Carver c(nullptr);
-    c.take<char>(gws);
-    c.take<float>((size_t)n);
-    c.take<int32_t>(1);
-    KKM_HIP(hipMalloc(&block, c.bytes()));
+    auto block_bytes = [&]() {
+        Carver c(nullptr);
+        c.take<char>(gws);
+        c.take<float>((size_t)n);  // diag
+        c.take<int32_t>(1);        // non-finite flag
+        return c.bytes();
+    };
+    if (hipMalloc(&block, block_bytes()) != hipSuccess) {  // without the split it may fit
+        (void)hipGetLastError();
+        gws = gram_workspace_bytes(n, d, gram_prec, false);
+        KKM_HIP(hipMalloc(&block, block_bytes()));
+    }
     KKM_HIP(hipHostMalloc((void **)&hflag, sizeof(int32_t), hipHostMallocDefault));
     Carver w(block);
     void *gram_ws = w.take<char>(gws);
