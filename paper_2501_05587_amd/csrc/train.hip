@@ -86,25 +86,13 @@ __device__ __forceinline__ void batch_kernel_tile(const TrainStep &t, int64_t ti
         small_load<true, FK>(x, n0, k0, rb);
     };
     load(0);
-    if (t.kern.kernel == KKM_GAUSS) {
-        // the squared norms of the 64 rows, eight per wave, a wave per row at a time
-        float s[8];
+    // the squared norms of the 64 rows, eight per wave, a wave per row at a
+    // time, from the staged rows (zeros past d add nothing)
+    float s8[8];
 #pragma unroll
-        for (int u = 0; u < 8; ++u) s[u] = 0.f;
-        const int first = wave * 8;
-        const int64_t base = first < ST ? m0 + first : n0 + first - ST;
-        for (int64_t l = lane; l < t.d; l += kWave)
-#pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                const float x = t.XB[min(base + u, t.B - 1) * t.ldx + l];
-                s[u] = fmaf(x, x, s[u]);
-            }
-#pragma unroll
-        for (int u = 0; u < 8; ++u) {
-            s[u] = wave_sum(s[u]);
-            if (lane == 0) lds.f.nrm[first + u] = s[u];
-        }
-    }
+    for (int u = 0; u < 8; ++u) s8[u] = 0.f;
+    const int first = wave * 8;
+    const float *nrow = first < ST ? lds.f.a[first] : lds.f.b[first - ST];
     f32x4 acc = {0.f, 0.f, 0.f, 0.f};
     const int kq = (q >> 1) + 16 * (q & 1);
     for (int64_t k0 = 0; k0 < t.d; k0 += FK) {
@@ -119,12 +107,27 @@ __device__ __forceinline__ void batch_kernel_tile(const TrainStep &t, int64_t ti
         }
         __syncthreads();
         if (k0 + FK < t.d) load(k0 + FK);
+        if (t.kern.kernel == KKM_GAUSS)
+            for (int l = lane; l < klim; l += kWave)
+#pragma unroll
+                for (int u = 0; u < 8; ++u) {
+                    const float x = nrow[u * FLDK + l];
+                    s8[u] = fmaf(x, x, s8[u]);
+                }
         if (wave < 4) {
             const float *pa = &lds.f.a[wm + i][kq], *pb = &lds.f.b[wn + i][kq];
             for (int s = 0; s < klim; s += 32)
 #pragma unroll
                 for (int u = 0; u < 8; ++u)
                     acc = __builtin_amdgcn_mfma_f32_16x16x4f32(pa[s + 2 * u], pb[s + 2 * u], acc, 0, 0, 0);
+        }
+        __syncthreads();
+    }
+    if (t.kern.kernel == KKM_GAUSS) {
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            s8[u] = wave_sum(s8[u]);
+            if (lane == 0) lds.f.nrm[first + u] = s8[u];
         }
         __syncthreads();
     }
@@ -221,7 +224,7 @@ __global__ __launch_bounds__(SNT) void train_loss(TrainStep t, int kc, float alp
 #pragma unroll
         for (int r = 0; r < 4; ++r) kb[u][r] = t.KB[min(r0 + 4 * q + r, (int64_t)(B - 1)) * t.ldkb + c];
     }
-    const int kv = kc / 4;
+    const int kv = kc / 4, dr = SNT / kv, dk = SNT % kv;
     const bool vec = (t.out & 3) == 0;  // Phi is the workspace's own, 256-byte aligned
     // the sums of NT of the wave's tiles over the staged columns
     auto sums = [&](auto tiles, int klim) {
@@ -244,19 +247,27 @@ __global__ __launch_bounds__(SNT) void train_loss(TrainStep t, int kc, float alp
     const int mine = (nt - wave + SNT / kWave - 1) / (SNT / kWave);  // tiles of this wave (<= 0: none)
     for (int64_t k0 = 0; k0 < t.out; k0 += kc) {
         auto stage = [&](auto vector) {
-            for (int e0 = tid; e0 < 16 * nt * kv; e0 += 8 * SNT) {  // eight loads in flight
+            int r = tid / kv, k = tid % kv;  // stepped, not divided
+            while (r < 16 * nt) {            // eight loads in flight
                 f32x4 v[8];
+                int rr[8], kk[8];
 #pragma unroll
                 for (int u = 0; u < 8; ++u) {
-                    const int e = e0 + u * SNT, r = e / kv, k = 4 * (e % kv);
-                    v[u] = line4<decltype(vector)::value>(t.Phi, r * t.out, k0 + k, t.out, r < B);
+                    rr[u] = r;
+                    kk[u] = 4 * k;
+                    v[u] = line4<decltype(vector)::value>(t.Phi, r * t.out, k0 + kk[u], t.out, r < B);
+                    r += dr;
+                    k += dk;
+                    if (k >= kv) {
+                        k -= kv;
+                        ++r;
+                    }
                 }
 #pragma unroll
-                for (int u = 0; u < 8; ++u) {
-                    const int e = e0 + u * SNT, r = e / kv, k = 4 * (e % kv);
-                    if (r < 16 * nt)
-                        *reinterpret_cast<f32x4 *>(&phi[r * ld + k]) = mask4(v[u], k0 + k, t.out, r < B);
-                }
+                for (int u = 0; u < 8; ++u)
+                    if (rr[u] < 16 * nt)
+                        *reinterpret_cast<f32x4 *>(&phi[rr[u] * ld + kk[u]]) =
+                            mask4(v[u], k0 + kk[u], t.out, rr[u] < B);
             }
         };
         if (vec)
@@ -298,7 +309,9 @@ __global__ __launch_bounds__(SNT) void train_loss(TrainStep t, int kc, float alp
         for (int w = 0; w < SNT / kWave; ++w) s += red[w];
         t.part[blockIdx.x] = s;
     }
-    // dPhi: k runs over the batch, 16 steps of 4 in flight
+    // dPhi: k runs over the batch, 16 steps of 4 in flight; Phi from LDS where
+    // all its columns are staged (rows past the batch are zeros there)
+    const bool whole = kc >= t.out;
     for (int64_t c0 = 16 * wave; c0 < t.out; c0 += 16 * (SNT / kWave)) {
         const int64_t c = c0 + i;
         f32x4 d = {0.f, 0.f, 0.f, 0.f};
@@ -307,7 +320,11 @@ __global__ __launch_bounds__(SNT) void train_loss(TrainStep t, int kc, float alp
 #pragma unroll
             for (int u = 0; u < 16; ++u) {
                 const int k = s + 4 * u + q;
-                const float x = t.Phi[min(k, B - 1) * t.out + min(c, t.out - 1)];
+                float x;
+                if (whole)  // uniform
+                    x = phi[min(k, B - 1) * ld + min((int)c, ld - 1)];
+                else
+                    x = t.Phi[min(k, B - 1) * t.out + min(c, t.out - 1)];
                 b[u] = k < B ? x : 0.f;
             }
 #pragma unroll
