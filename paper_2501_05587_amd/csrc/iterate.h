@@ -101,4 +101,19 @@ kkm_status vcsr_build(const int32_t *labels, int64_t n, int32_t k, int32_t *blk_
                       int32_t *offsets, int32_t *counts_out, int64_t *n_changed,
                       hipStream_t stream);
 
+// Bits needed for labels in [0, k).
+__device__ __forceinline__ int label_bits(int32_t k) { return k > 1 ? 32 - __clz(k - 1) : 0; }
+
+// The wave's valid lanes holding the same label as this one: one ballot per
+// label bit (a ballot per distinct label took up to min(k, 64) rounds).
+__device__ __forceinline__ uint64_t label_peers(bool valid, int32_t c, int bits) {
+    uint64_t peers = __ballot(valid);
+    for (int b = 0; b < bits; ++b) {
+        const bool one = (c >> b) & 1;
+        const uint64_t m = __ballot(one);
+        peers &= one ? m : ~m;
+    }
+    return peers;
+}
+
 }  // namespace kkm

@@ -61,21 +61,6 @@ __device__ __forceinline__ bool locate(const InstSet &s, const int64_t *start, i
 
 // ---------------------------------------------------------------- 1. V in CSR form
 
-// Bits needed for labels in [0, k).
-__device__ __forceinline__ int label_bits(int32_t k) { return k > 1 ? 32 - __clz(k - 1) : 0; }
-
-// The wave's valid lanes holding the same label as this one: one ballot per
-// label bit (a ballot per distinct label took up to min(k, 64) rounds).
-__device__ __forceinline__ uint64_t label_peers(bool valid, int32_t c, int bits) {
-    uint64_t peers = __ballot(valid);
-    for (int b = 0; b < bits; ++b) {
-        const bool one = (c >> b) & 1;
-        const uint64_t m = __ballot(one);
-        peers &= one ? m : ~m;
-    }
-    return peers;
-}
-
 // Per-block label histogram (column-major [k][nblk]) and range check.
 template <bool MULTI>
 __global__ __launch_bounds__(kPtsPerBlock) void v_block_hist(InstSet s, const int32_t *labels_all) {
