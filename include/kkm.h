@@ -436,9 +436,9 @@ size_t kkm_kernel_kmeanspp_workspace_bytes(int64_t n, int32_t k);
  *   restarts      >= 1 seedings; restart r draws with uniforms[r*k .. r*k+k)
  *                 (host double, each in [0, 1)).
  *   max_iter      >= 0 Lloyd steps per restart.
- *   streams       >= 1: the restarts run on this many internal streams of
- *                 default priority, one host thread each; the result is the
- *                 same for every value.
+ *   streams       >= 1: the restarts run on this many streams, the caller's
+ *                 and internal ones of default priority, one host thread
+ *                 each; the result is the same for every value.
  *   labels_out    [n] int32 (device) the chosen labelling.
  *   objective, cheap_iters, best_restart   host, nullable: the chosen
  *                 restart's feature-space objective, the Lloyd steps summed
