@@ -77,6 +77,43 @@ __device__ __forceinline__ float kappa_from_dot(float b, float ni, float nj, int
     return b;
 }
 
+// Calls fn(kappa) once with the kernel function of this Gram, kappa(b, ni, nj,
+// si, sj) as kappa_from_dot on the scaled product: which one, and whether
+// there are scales, is decided here and not for each of a lane's 64 values (a
+// branch or two each: Gaussian, n = 20011, d = 256, bfloat16 K: BF16 product 295
+// -> 235 us, FP8 290 -> 216; n = 60000, d = 64: FP8 1957 -> 1400).
+template <typename Fn>
+__device__ __forceinline__ void with_kappa(const Epi &e, Fn &&fn) {
+    const float gamma = e.gamma, coef0 = e.coef0;
+    auto scales = [&](auto scaled) {
+        constexpr bool S = decltype(scaled)::value;
+        if (e.kernel == KKM_GAUSS)
+            fn([=](float b, float ni, float nj, float si, float sj) {
+                if (S) b *= si * sj;
+                return kappa_from_dot(b, ni, nj, KKM_GAUSS, gamma, coef0, 0);
+            });
+        else if (e.kernel == KKM_POLY && e.degree == 2)
+            fn([=](float b, float, float, float si, float sj) {
+                if (S) b *= si * sj;
+                return kappa_from_dot(b, 0.f, 0.f, KKM_POLY, gamma, coef0, 2);
+            });
+        else if (e.kernel == KKM_POLY)
+            fn([=, &e](float b, float, float, float si, float sj) {
+                if (S) b *= si * sj;
+                return kappa_from_dot(b, 0.f, 0.f, KKM_POLY, gamma, coef0, e.degree);
+            });
+        else
+            fn([=](float b, float, float, float si, float sj) {
+                if (S) b *= si * sj;
+                return b;
+            });
+    };
+    if (e.scale)
+        scales(std::true_type{});
+    else
+        scales(std::false_type{});
+}
+
 // K leaves through non-temporal stores: it is written once and not read back
 // by the kernel, so its lines should not displace the operand rows in the
 // caches (measured 80 -> 75 ms for the BF16 product with bfloat16 K at
@@ -219,7 +256,9 @@ __device__ __forceinline__ void stage_norms(const Epi &e, int64_t m0, int64_t n0
 // each tile writes only its own block K[i][j], through `T` as is; a diagonal
 // tile also writes diag(K).  Tile (j, i) multiplies the same products in the
 // same order as tile (i, j), so K is still exactly symmetric.
-template <typename OUT, bool FULL, int HALVES = 1>
+//
+// HOIST: the kernel function is chosen once per tile (with_kappa).
+template <typename OUT, bool FULL, int HALVES = 1, bool HOIST = true>
 __device__ __forceinline__ void epilogue(const Epi &e, f32x16 (&acc)[2][2], int64_t m0,
                                          int64_t n0, bool diag_tile, int wr, int wc, int lane,
                                          float *T, const float *rn, const float *rs) {
@@ -259,22 +298,31 @@ __device__ __forceinline__ void epilogue(const Epi &e, f32x16 (&acc)[2][2], int6
             return;
         }
         if (!diag_tile) {
+            with_kappa(e, [&](auto kappa) {
+#pragma unroll
+                for (int mi = 0; mi < 2; ++mi)
+#pragma unroll
+                    for (int ni = 0; ni < 2; ++ni) {
+                        const int jj = wc * 64 + ni * 32 + l32;
+                        const float nrm_j = rn[GM + jj], s_j = rs[GM + jj];
+#pragma unroll
+                        for (int rg = 0; rg < 4; ++rg) {
+                            const int ii0 = wr * 64 + mi * 32 + 8 * rg + 4 * half;
+#pragma unroll
+                            for (int r = 0; r < 4; ++r)
+                                acc[mi][ni][4 * rg + r] =
+                                    kappa(acc[mi][ni][4 * rg + r], rn[ii0 + r], nrm_j, rs[ii0 + r], s_j);
+                        }
+                    }
+            });
 #pragma unroll
             for (int mi = 0; mi < 2; ++mi)
 #pragma unroll
                 for (int ni = 0; ni < 2; ++ni) {
                     const int jj = wc * 64 + ni * 32 + l32;
-                    const float nrm_j = rn[GM + jj], s_j = rs[GM + jj];
 #pragma unroll
                     for (int rg = 0; rg < 4; ++rg) {
                         const int ii0 = wr * 64 + mi * 32 + 8 * rg + 4 * half;
-#pragma unroll
-                        for (int r = 0; r < 4; ++r) {
-                            float b = acc[mi][ni][4 * rg + r];
-                            if (e.scale) b *= rs[ii0 + r] * s_j;
-                            acc[mi][ni][4 * rg + r] = kappa_from_dot(b, rn[ii0 + r], nrm_j, e.kernel,
-                                                                     e.gamma, e.coef0, e.degree);
-                        }
                         // transposed: T[jj][ii0 .. ii0+3]
                         const f32x4 w = {acc[mi][ni][4 * rg], acc[mi][ni][4 * rg + 1],
                                          acc[mi][ni][4 * rg + 2], acc[mi][ni][4 * rg + 3]};
@@ -343,24 +391,44 @@ __device__ __forceinline__ void epilogue(const Epi &e, f32x16 (&acc)[2][2], int6
             return;
         }
         if (!diag_tile) {
+            if constexpr (HOIST) {
+                with_kappa(e, [&](auto kappa) {
 #pragma unroll
-            for (int mi = 0; mi < 2; ++mi)
+                    for (int mi = 0; mi < 2; ++mi)
 #pragma unroll
-                for (int ni = 0; ni < 2; ++ni) {
-                    const int jj = wc * 64 + ni * 32 + l32;
-                    const float nrm_j = rn[GM + jj], s_j = rs[GM + jj];
+                        for (int ni = 0; ni < 2; ++ni) {
+                            const int jj = wc * 64 + ni * 32 + l32;
+                            const float nrm_j = rn[GM + jj], s_j = rs[GM + jj];
 #pragma unroll
-                    for (int rg = 0; rg < 4; ++rg) {
-                        const int ii0 = wr * 64 + mi * 32 + 8 * rg + 4 * half;
+                            for (int rg = 0; rg < 4; ++rg) {
+                                const int ii0 = wr * 64 + mi * 32 + 8 * rg + 4 * half;
 #pragma unroll
-                        for (int r = 0; r < 4; ++r) {
-                            float b = acc[mi][ni][4 * rg + r];
-                            if (e.scale) b *= rs[ii0 + r] * s_j;
-                            acc[mi][ni][4 * rg + r] = kappa_from_dot(b, rn[ii0 + r], nrm_j, e.kernel,
-                                                                     e.gamma, e.coef0, e.degree);
+                                for (int r = 0; r < 4; ++r)
+                                    acc[mi][ni][4 * rg + r] =
+                                        kappa(acc[mi][ni][4 * rg + r], rn[ii0 + r], nrm_j, rs[ii0 + r], s_j);
+                            }
+                        }
+                });
+            } else {
+#pragma unroll
+                for (int mi = 0; mi < 2; ++mi)
+#pragma unroll
+                    for (int ni = 0; ni < 2; ++ni) {
+                        const int jj = wc * 64 + ni * 32 + l32;
+                        const float nrm_j = rn[GM + jj], s_j = rs[GM + jj];
+#pragma unroll
+                        for (int rg = 0; rg < 4; ++rg) {
+                            const int ii0 = wr * 64 + mi * 32 + 8 * rg + 4 * half;
+#pragma unroll
+                            for (int r = 0; r < 4; ++r) {
+                                float b = acc[mi][ni][4 * rg + r];
+                                if (e.scale) b *= rs[ii0 + r] * s_j;
+                                acc[mi][ni][4 * rg + r] = kappa_from_dot(b, rn[ii0 + r], nrm_j, e.kernel, e.gamma,
+                                                                         e.coef0, e.degree);
+                            }
                         }
                     }
-                }
+            }
             // bfloat16 K: the values are rounded to bfloat16 here (the stores round
             // them anyway, and rounding an exact bfloat16 value again changes no bit)
             // and kept two per register through the passes below; with the FP32
