@@ -79,8 +79,8 @@ TRAFFIC = {
                        "fetch_scale": 1.9999, "write_scale": 1.0},
     "gram_split_mfma": {"sources": ["csrc/gram.hip", "csrc/gram_split.hip", "csrc/gram_split.h",
                                     "csrc/gram_tile.h", "csrc/kkm_common.h"],
-                        "sha256": "47a16555fdf31ce887f6d7495ed66ae8b2097bc2d73aa13a6a6aef80bd3694d8",
-                        "n": 200000, "fetch_kib": 323987273.1, "write_kib": 169198847.7,
+                        "sha256": "39ea43c1d36037e6014cfe7ed50f6cc09786922c20b96754a7d68e93b9d122db",
+                        "n": 200000, "fetch_kib": 319955168.6, "write_kib": 169139403.1,
                         "fetch_scale": 1.9999, "write_scale": 1.0},
 }
 
