@@ -451,12 +451,13 @@ extern "C" kkm_status kkm_mlp_train_fresh(float *params, float *adam_m, float *a
     KKM_TRY(check_kernel(kernel_type, gamma, coef0, degree));
     size_t need = 0;
     TrainWs w = carve_train(ws, m, B, &need);
-    const size_t gws = gram_workspace_bytes(B, d, KKM_F32);
-    if (!ws || ws_bytes < need + gws) {
-        set_error("kkm_mlp_train_fresh: workspace of %zu bytes is smaller than %zu", ws_bytes,
-                  need + gws);
+    // without room for the split parts of a large batch the FP32 Gram kernel runs
+    const size_t least = need + gram_workspace_bytes(B, d, KKM_F32, false);
+    if (!ws || ws_bytes < least) {
+        set_error("kkm_mlp_train_fresh: workspace of %zu bytes is smaller than %zu", ws_bytes, least);
         return KKM_ERR_NOMEM;
     }
+    const size_t gws = ws_bytes - need;
     void *gram_ws = static_cast<char *>(ws) + need;
     hipStream_t s = (hipStream_t)stream;
     for (int32_t st = 0; st < steps; ++st) {
