@@ -994,9 +994,14 @@ __global__ __launch_bounds__(NW *kWave) void assign_fused(InstSet s, const int32
         }
     }
     __syncthreads();
-    for (int c = tid; c < k; c += NT) part_store<SMALL>(assign_sizes(in, c) + lb, (uint8_t)hist[c]);
-    if constexpr (SMALL) {
-        __syncthreads();  // every part of this workgroup is stored before its arrival
+    if constexpr (!SMALL) {
+        for (int c = tid; c < k; c += NT) part_store<SMALL>(assign_sizes(in, c) + lb, (uint8_t)hist[c]);
+    } else {
+        // every part leaves by the wave whose first lane then arrives, so that its
+        // release waits for all of them: a wave waits for its own stores only, and
+        // a barrier for none
+        if (wave == 0)
+            for (int c = lane; c < k; c += kWave) part_store<SMALL>(assign_sizes(in, c) + lb, (uint8_t)hist[c]);
         if (tid == 0)
             last = __hip_atomic_fetch_add(in.err + 1, 1, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT) ==
                    (int32_t)assign_blocks(in) - 1;

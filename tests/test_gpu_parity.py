@@ -314,3 +314,22 @@ def test_step_routes(kkm, n, k, pad, bf16):
     bad[n // 2] = k
     r = kkm.kkm_iterate(Kd, diag, to_dev(bad), k)
     assert int(r[2].item()) == -1
+
+
+# sizes that the last workgroup of the assignment to arrive adds up from every
+# other's: k past a wave's width, one to 128 workgroups, the same buffers again
+# with other labels, so that a part that was not there yet would be an old one
+@pytest.mark.parametrize("n,k", [(65, 65), (1023, 65), (1024, 128), (1500, 129), (2049, 192), (2049, 256), (8192, 70)])
+def test_step_sizes_of_repeated_steps(kkm, n, k):
+    import torch
+    g = torch.Generator(device="cuda")
+    g.manual_seed(n + k)
+    K = torch.randn(n, n, generator=g, device="cuda")
+    K = K + K.T
+    diag = K.diagonal().contiguous()
+    ws = torch.empty(kkm.iterate_workspace_bytes(n, k), dtype=torch.uint8, device="cuda")
+    say("  step sizes", n, k)
+    for _ in range(40):
+        labels = torch.randint(k, (n,), generator=g, device="cuda").to(torch.int32)
+        lab, cnt = kkm.kkm_iterate(K, diag, labels, k, ws=ws)[:2]
+        assert torch.equal(cnt.long(), torch.bincount(lab.long(), minlength=k))
