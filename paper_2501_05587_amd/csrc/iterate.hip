@@ -189,6 +189,14 @@ __global__ __launch_bounds__(kPtsPerBlock) void v_scatter(InstSet s, const int32
 // same V.
 constexpr int kSmallGroups = kSmallPts / kSmallThreads;  // 64-point groups per wave
 
+// What the wave's lanes read and wrote in LDS before it comes before what they
+// read and write after it.
+__device__ __forceinline__ void wave_fence() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 __global__ __launch_bounds__(kSmallThreads) void v_csr_small(Inst in, const int32_t *labels) {
     extern __shared__ int32_t sh[];  // run[k], wcnt[16][k]
     __shared__ int32_t bad;
@@ -218,11 +226,12 @@ __global__ __launch_bounds__(kSmallThreads) void v_csr_small(Inst in, const int3
         nbad += __popcll(__ballot(in_n && !valid));
         const uint64_t peers = label_peers(valid, c[g], bits);
         const int32_t below = __popcll(peers & ((lane == 0) ? 0ull : (~0ull >> (64 - lane))));
-        if (valid) {
-            const int32_t before = wcnt[wave * k + c[g]];  // read by the group's lanes,
-            rank[g] = before + below;
-            if (below == 0) wcnt[wave * k + c[g]] = before + __popcll(peers);  // then its first writes
-        }
+        int32_t *const count = &wcnt[wave * k + (valid ? c[g] : 0)];
+        const int32_t before = *count;  // read by a label's lanes,
+        rank[g] = before + below;
+        wave_fence();
+        if (valid && below == 0) *count = before + __popcll(peers);  // then written by its first
+        wave_fence();
     }
     if (nbad && lane == 0) atomicAdd(&bad, nbad);
     __syncthreads();

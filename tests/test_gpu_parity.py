@@ -333,3 +333,29 @@ def test_step_sizes_of_repeated_steps(kkm, n, k):
         labels = torch.randint(k, (n,), generator=g, device="cuda").to(torch.int32)
         lab, cnt = kkm.kkm_iterate(K, diag, labels, k, ws=ws)[:2]
         assert torch.equal(cnt.long(), torch.bincount(lab.long(), minlength=k))
+
+
+# V of a small problem by one workgroup: a wave's 64 points of one label, of 64
+# labels, and runs that end inside a wave, in each of its groups of points
+@pytest.mark.parametrize("n", [64, 1025, 4096, 8191])
+@pytest.mark.parametrize("order", ["one", "cycle", "runs"])
+def test_step_label_orders(kkm, n, order):
+    import torch
+    k = 64
+    i = torch.arange(n, device="cuda")
+    labels = {"one": i * 0 + 3, "cycle": i % k, "runs": (i // 37) % k}[order].to(torch.int32)
+    # K_ij = v_i v_j of small whole numbers: every sum is exact in float32
+    v = ((i * 7) % 13 - 6).float()
+    K = v[:, None] * v[None, :]
+    D = torch.empty(n, k, device="cuda")
+    say("  label orders", n, order)
+    kkm.kkm_iterate(K, v * v, labels, k, D_out=D)
+    cnt = torch.bincount(labels.long(), minlength=k).double()
+    sums = torch.zeros(k, dtype=torch.float64, device="cuda").index_add_(0, labels.long(), v.double())
+    mean = sums / cnt
+    want = (v.double()[:, None] - mean[None, :]).square()
+    # |v| <= 6: an average, its product with v and the norm are each rounded once
+    # or twice, and D three times more, at values of at most 144
+    live = cnt > 0
+    assert bool(((D.double() - want)[:, live].abs() <= 8 * 144 * 2.0 ** -24).all())
+    assert bool(torch.isinf(D[:, ~live]).all())
