@@ -390,8 +390,9 @@ __global__ __launch_bounds__(256) void matfree_sweep(MfArgs a, Inst in, const in
 // double-buffered, the next tile's rows and the one after's indices in flight
 // meanwhile).  With both operands staged per tile the sweep waited for gathered
 // rows with one workgroup per CU (241 VGPRs + 64 AGPRs); here a 32 x 32 block
-// needs 16 accumulators and no cross-wave flush, two to four workgroups share a
-// CU, and the bound is the vector ALU: per kernel value a sum of norms, a
+// needs 16 accumulators and no barrier per flush (the waves' own-cluster sums of
+// a tile's flushes meet in LDS and leave, one per strip, after the barrier that
+// ends the tile), two to four workgroups share a CU, and the bound is the vector ALU: per kernel value a sum of norms, a
 // multiply-add, a clamp, a multiply, a quarter-rate exponential and a sum.
 // Step at n = 50021, d = 128, k = 32, Gaussian, BF16: 4.15 -> 0.94 ms; at
 // n = 20000: BF16 d = 256 1.02 -> 0.38 ms, FP8 d = 256 0.94 -> 0.28 ms, FP32
@@ -407,6 +408,8 @@ template <int NS> struct MrLds {
     static constexpr int LD = NS * SLAB + 16;  // padded row: b128 reads of 32 rows spread over all banks
     alignas(16) unsigned char op[2][mr_rows<NS>() * LD];
     alignas(16) float rn[2][64], rs[2][64];    // norms / scales of the tile's positions
+    alignas(16) float z[2][64][4];             // own-cluster sums of the tile's flushes, one per wave
+    int32_t zc[2][64];                         // their clusters
 };
 
 template <int PREC, int NS, int KERN>
@@ -433,8 +436,7 @@ __global__ __launch_bounds__(256, NS <= 2 ? 3 : 2) void matfree_resident(MfArgs 
     const int lane = tid & 63;
     const int wave = tid >> 6;
     const int half = lane >> 5, l32 = lane & 31;
-    const int64_t wstrip = strip * (MF_N / MR_WAVE) + wave;  // 32-point strip of this wave
-    const int64_t my_i = wstrip * MR_WAVE + l32;
+    const int64_t my_i = strip * MF_N + wave * MR_WAVE + l32;
     const bool in_n = my_i < n;
     const int32_t my_lab = in_n ? labels[my_i] : -1;
     const float nB = in_n ? a.nrm[my_i] : 0.f;
@@ -500,6 +502,8 @@ __global__ __launch_bounds__(256, NS <= 2 ? 3 : 2) void matfree_resident(MfArgs 
     int32_t c_end = offsets[c + 1];
 
     float run = 0.f, comp = 0.f;
+    int buf = 0, nf = 0;  // the tile's buffers, and its flushes so far (at most one per position)
+    static_assert(MF_N == 4 * MR_WAVE && MR <= 64, "four waves, at most 64 flushes a tile");
     auto flush = [&](int32_t cl) {
         // lanes l and l + 32 hold the same point: fold the upper half in
         const float os = __shfl_xor(run, 32, kWave);
@@ -513,8 +517,20 @@ __global__ __launch_bounds__(256, NS <= 2 ? 3 : 2) void matfree_resident(MfArgs 
             if (my_lab == cl) z = tot;
         }
         z = wave_sum(z);
-        if (lane == 0 && wstrip < in.nws) in.Zp[(q + cl) * in.nws + wstrip] = z;
+        if (lane == 0) {
+            lds.z[buf][nf][wave] = z;
+            if (wave == 0) lds.zc[buf][nf] = cl;
+        }
+        ++nf;  // the same for every wave
         run = comp = 0.f;
+    };
+    // the strip's own-cluster sums of the tile's flushes, after the barrier that ends it
+    auto drain = [&]() {
+        if (tid < nf) {
+            const f32x4 z = *reinterpret_cast<const f32x4 *>(lds.z[buf][tid]);
+            in.Zp[(q + lds.zc[buf][tid]) * in.nws + strip] = (z[0] + z[1]) + (z[2] + z[3]);
+        }
+        nf = 0;
     };
 
     load_idx(p_begin);
@@ -621,7 +637,6 @@ __global__ __launch_bounds__(256, NS <= 2 ? 3 : 2) void matfree_resident(MfArgs 
         }
     };
 
-    int buf = 0;
     for (int32_t p0 = p_begin; p0 < p_end; p0 += MR) {
         const bool more = p0 + MR < p_end;
         if (more) {
@@ -645,11 +660,10 @@ __global__ __launch_bounds__(256, NS <= 2 ? 3 : 2) void matfree_resident(MfArgs 
             block_kappa(buf, 0, v);
             block_segments(v, p0, min(p0 + 32, p_end));
         }
-        if (more) {
-            store_rows_lds(buf ^ 1);
-            __syncthreads();  // the next tile is staged and every read of this one is done
-            buf ^= 1;
-        }
+        if (more) store_rows_lds(buf ^ 1);
+        __syncthreads();  // the next tile is staged, every read of this one is done, its sums are there
+        drain();
+        buf ^= 1;
     }
 }
 
@@ -735,7 +749,6 @@ struct MfLayout {
     InstGeom g;
     int64_t nstrip, dpad;
     bool resident;  // the sweep that keeps the points' rows in registers
-    int64_t nws;    // own-cluster sums per slot: one per wave (32 points) or per strip
     size_t inst_bytes, zp_floats, xq_bytes;
 };
 
@@ -746,8 +759,7 @@ MfLayout mf_layout(int64_t n, int64_t d, int32_t k, int32_t gram_prec) {
     m.dpad = (gram_prec == KKM_F32) ? d : padded_d(d, gram_prec);
     m.inst_bytes = inst_workspace_bytes(m.g);
     m.resident = mf_slabs(d, gram_prec) <= MR_MAX_SLABS;
-    m.nws = m.resident ? (n + MR_WAVE - 1) / MR_WAVE : m.nstrip;
-    m.zp_floats = (size_t)m.g.slots * (size_t)m.nws;
+    m.zp_floats = (size_t)m.g.slots * (size_t)m.nstrip;
     m.xq_bytes = (gram_prec == KKM_F32) ? 0
                  : (size_t)n * (size_t)m.dpad * ((gram_prec == KKM_BF16) ? 2 : 1);
     return m;
@@ -830,7 +842,7 @@ kkm_status mf_step(const MfArgs &a, int32_t gram_prec, const MfLayout &m, const 
     in.D_out = D_out;
     in.ctilde_out = ctilde_out;
     in.nstrip = m.nstrip;
-    in.nws = m.nws;
+    in.nws = m.nstrip;
     in.Zp = w.Zp;
     const int64_t items = m.nstrip * m.g.nchunk;
     if (items > 0x7fffffff) {

@@ -78,6 +78,17 @@ def test_workspace_sizes(lib):
     assert kkm.gram_workspace_bytes(1000, 16) >= 1000 * 4
 
 
+def test_matfree_workspace_size_of_the_longest_rows_serves_shorter_ones():
+    # the FP32 product reads the caller's rows: what a step needs depends on n and
+    # k alone, whichever sweep the row length takes
+    import paper_2501_05587_amd as kkm
+    for n, k in ((1, 1), (100, 3), (4097, 16), (50000, 32), (200000, 64)):
+        sizes = [kkm.matfree_workspace_bytes(n, d, k, kkm.F32) for d in (1, 32, 33, 256, 257, 1000)]
+        assert len(set(sizes)) == 1, (n, k, sizes)
+    # a buffer of the size that the sweep of longer rows has always asked for
+    assert kkm.matfree_workspace_bytes(50000, 128, 32, kkm.F32) <= 12374784
+
+
 def test_instance_struct_layout_matches_header(tmp_path):
     """The ctypes mirror of kkm_instance has the C struct's size and offsets."""
     import subprocess
