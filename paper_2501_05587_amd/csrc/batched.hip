@@ -387,7 +387,10 @@ void make_plan(const kkm_instance *inst, int32_t count, int32_t gram_prec, int32
     if (split && gram_prec == KKM_F32 && (reinterpret_cast<uintptr_t>(base) & 15) == 0) {
         p.split_flags = c.take<int32_t>((size_t)count);
         for (int32_t b = 0; b < count; ++b)
-            if (split_pays(inst[b].n, inst[b].d)) Xs[b] = c.take<unsigned char>(split_bytes(inst[b].n, inst[b].d));
+            if (split_room(inst[b].n, inst[b].d)) {
+                unsigned char *at = c.take<unsigned char>(split_bytes(inst[b].n, inst[b].d));
+                if (split_pays(inst[b].n, inst[b].d)) Xs[b] = at;
+            }
     }
     p.bytes = c.bytes();
 

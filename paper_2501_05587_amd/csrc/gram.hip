@@ -68,7 +68,7 @@ int group_log2(int64_t d, int32_t gram_prec) {
 size_t gram_workspace_bytes(int64_t n, int64_t d, int32_t gram_prec, bool split) {
     Carver c(nullptr);
     c.take<float>((size_t)n);  // squared norms
-    if (gram_prec == KKM_F32 && split && split_pays(n, d)) {
+    if (gram_prec == KKM_F32 && split && split_room(n, d)) {
         c.take<int32_t>(1);  // flag: values left to the FP32 kernel
         c.take<unsigned char>(split_bytes(n, d));
     }

@@ -1,15 +1,27 @@
 // The FP32 product of the kernel matrix on the bfloat16 matrix units: every
-// FP32 value is the sum of three bfloat16 values, x = h + m + l (each the
-// rounding of what the ones before left; the remainder is below 2^-26 |x|), and
-//   x y = (h h' + (h m' + m h') + (m m' + h l' + l h')) + terms below 2^-25 |x y|
-// so six v_mfma_f32_32x32x16_bf16, their products exact and their sums FP32,
-// take the place of eight v_mfma_f32_32x32x2_f32 at a sixteenth of their cost
-// each (2.5 PFLOP/s against 157 TFLOP/s).  A sum is rounded six times per 16
-// features instead of sixteen times, and the error against 64 bits is smaller
-// (X X^T of normal points, n = 16384, relative in norm: d = 16 3.4e-8 where the
-// FP32 kernel has 7.3e-8, d = 128 8.1e-8 / 2.0e-7, d = 784 1.2e-7 / 5.0e-7).
+// FP32 value is the sum of three bfloat16 values, x = h + m + l exactly (each the
+// rounding of what the ones before left: 8 bits of the 24), and
+//   x y = h h' + (h m' + m h' + m m' + h l' + l h' + m l' + l m') + l l'
+// with l l' below 2^-33 |x y|.  Eight v_mfma_f32_32x32x16_bf16 with exact products
+// and FP32 sums take the place of eight v_mfma_f32_32x32x2_f32 at a sixteenth of
+// their cost each (2.5 PFLOP/s against 157 TFLOP/s).
 //
-// n = 60000, d = 784: 25.8 -> 15.8 ms, 1.07 PFLOP/s of bfloat16 products, the
+// The products h h' have sums of their own, a slab's 32 features from zero and
+// the slabs' rounded to nearest: these products have 16 bits, so that FP32 adds a
+// few of them without rounding.  All the others are below 2^-6 of them, and the
+// roundings of their sum below 2^-29.  The two meet once, after the last slab.  So
+// a single product is rounded once, as the FP32 matrix unit rounds it, and a sum
+// less often: with one sum for all of them, a slab with one feature that both
+// rows have cost two roundings more, and sparse rows were less exact than on the
+// FP32 unit.  Without m l' and l m' (below 2^-24 |x y| together) a single product
+// was off by up to 1.5 times as much.
+// Error against 64 bits, relative in norm, of X X^T, n = 3600, here / FP32 matrix
+// unit / six products with one sum a slab: normal points d = 16 3.2e-8 / 7.4e-8 /
+// 3.4e-8, d = 128 5.5e-8 / 2.0e-7 / 8.0e-8, d = 784 1.0e-7 / 4.9e-7 / 1.2e-7; one
+// entry in five not zero d = 64 2.7e-8 / 3.9e-8 / 5.1e-8, d = 784 5.3e-8 / 1.2e-7 /
+// 9.8e-8; one feature 2.5e-8 / 2.5e-8 / 3.5e-8.
+//
+// n = 60000, d = 784: 25.4 -> 18.4 ms, 1.23 PFLOP/s of bfloat16 products, the
 // rate that a plain bfloat16 product of 8192^3 reaches on this card (1.13).
 //
 // Values whose low parts would leave the bfloat16 range, and infinities and
@@ -19,8 +31,8 @@
 //
 // Per 32-feature slab a 128 x 128 tile stages 2 x 24 KiB with direct
 // global-to-LDS loads, already in LDS order (the prologue wrote them so), single
-// buffered: three workgroups per CU hide each other's loads, as in the BF16
-// product.  A fragment feeds 6/3 as many MFMAs as there, so LDS is no bound.
+// buffered: two workgroups per CU (128 accumulators a lane) hide each other's
+// loads behind 64 MFMAs a wave and slab.  The bound is the matrix units' power.
 // Shared by the single- and many-instance Gram kernels.  Internal to the library.
 #pragma once
 
@@ -118,87 +130,92 @@ __device__ __forceinline__ void split_tile(const SplitTile &x, const Epi &e, int
         gb += x.slab_bytes;
     };
 
-    f32x16 acc[2][2];
+    // hi: the products h h'; lo: all the others
+    f32x16 hi[2][2], lo[2][2];
 #pragma unroll
     for (int i = 0; i < 2; ++i)
 #pragma unroll
         for (int j = 0; j < 2; ++j)
 #pragma unroll
-            for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+            for (int r = 0; r < 16; ++r) hi[i][j][r] = lo[i][j][r] = 0.f;
 
     stage_norms(e, m0, n0, lds.rn, lds.rs);
     // lane half h of MFMA s takes the 8 features of chunk 2s + h of its row
     const int swz = (l32 >> 2) & 3;
     const int frag = (l32 >> 4) * SPB + (l32 & 15) * 64;
     const unsigned char *As = lds.op[0] + wr * (4 * SPB) + frag, *Bs = lds.op[1] + wc * (4 * SPB) + frag;
+    auto frag_of = [&](const unsigned char *op, int i, int p, int chunk) {
+        return *reinterpret_cast<const bf16x8 *>(op + i * (2 * SPB) + p * SPP + chunk);
+    };
     for (int64_t kt = 0; kt < x.nslab; ++kt) {
         fetch();
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         __syncthreads();
-        const int chunk[2] = {(half ^ swz) * 16, ((2 + half) ^ swz) * 16};
-        bf16x8 b[2][2][3];  // [s][ni][plane]
 #pragma unroll
-        for (int s = 0; s < 2; ++s)
+        for (int s = 0; s < 2; ++s) {
+            const int chunk = ((2 * s + half) ^ swz) * 16;
+            // plane p of A's rows times plane q of B's
+            auto product = [&](int p, int q) {
+                bf16x8 a[2], b[2];
 #pragma unroll
-            for (int i = 0; i < 2; ++i)
+                for (int i = 0; i < 2; ++i) {
+                    a[i] = frag_of(As, i, p, chunk);
+                    b[i] = frag_of(Bs, i, q, chunk);
+                }
 #pragma unroll
-                for (int p = 0; p < 3; ++p)
-                    b[s][i][p] = *reinterpret_cast<const bf16x8 *>(Bs + i * (2 * SPB) + p * SPP + chunk[s]);
-        // A slab's 32 features are summed from zero and then added to the
-        // running sum: the matrix unit's own additions to a long sum cost more
-        // than the FP32 chain's at d = 784 (largest error of X X^T 1.4e-6 of its
-        // largest value against 1.3e-6; so 2.5e-7, for 4% of the time)
+                for (int mi = 0; mi < 2; ++mi)
+#pragma unroll
+                    for (int ni = 0; ni < 2; ++ni)
+                        lo[mi][ni] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[mi], b[ni], lo[mi][ni], 0, 0, 0);
+            };
+            // a mixed pair: a tile below the diagonal takes it the other way round
+            auto mixed = [&](int p, int q) {
+                const int u = FULL && bi > bj ? q : p, v = FULL && bi > bj ? p : q;
+                product(u, v);
+                product(v, u);
+            };
+            mixed(1, 2);  // the small terms first
+            mixed(0, 2);
+            product(1, 1);
+            mixed(0, 1);
+        }
+        // h h' of the slab, from zero, then rounded to nearest into the running sum:
+        // the matrix unit's own additions to a long sum cut it off
 #pragma unroll
         for (int mi = 0; mi < 2; ++mi) {
             f32x16 t[2];
 #pragma unroll
-            for (int ni = 0; ni < 2; ++ni)
+            for (int ni = 0; ni < 2; ++ni) {
 #pragma unroll
                 for (int r = 0; r < 16; ++r) t[ni][r] = 0.f;
 #pragma unroll
-            for (int s = 0; s < 2; ++s) {
-                bf16x8 a[3];
-#pragma unroll
-                for (int p = 0; p < 3; ++p)
-                    a[p] = *reinterpret_cast<const bf16x8 *>(As + mi * (2 * SPB) + p * SPP + chunk[s]);
-                auto product = [&](int p, int q) {
-#pragma unroll
-                    for (int ni = 0; ni < 2; ++ni)
-                        t[ni] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[p], b[s][ni][q], t[ni], 0, 0, 0);
-                };
-                if (FULL && bi > bj) {
-                    product(2, 0);
-                    product(0, 2);
-                    product(1, 1);
-                    product(1, 0);
-                    product(0, 1);
-                    product(0, 0);
-                } else {
-                    product(0, 2);  // the small terms first
-                    product(2, 0);
-                    product(1, 1);
-                    product(0, 1);
-                    product(1, 0);
-                    product(0, 0);
+                for (int s = 0; s < 2; ++s) {
+                    const int chunk = ((2 * s + half) ^ swz) * 16;
+                    t[ni] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_of(As, mi, 0, chunk), frag_of(Bs, ni, 0, chunk),
+                                                                    t[ni], 0, 0, 0);
                 }
             }
 #pragma unroll
             for (int ni = 0; ni < 2; ++ni)
 #pragma unroll
-                for (int r = 0; r < 16; ++r) acc[mi][ni][r] += t[ni][r];
+                for (int r = 0; r < 16; ++r) hi[mi][ni][r] += t[ni][r];
         }
         __syncthreads();  // every read of the slab is done
     }
+    f32x16(&acc)[2][2] = hi;
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[i][j][r] += lo[i][j][r];
     static_assert(sizeof(lds.op) >= epi_lds_bytes(2), "epilogue tile does not fit");
     static_assert(sizeof(lds.op) >= epi_lds_bytes_bf16, "bfloat16 epilogue tile does not fit");
     float *T = reinterpret_cast<float *>(&lds.op[0][0]);
-    // the kernel function chosen per value: chosen per tile, its copies of the
-    // loop made this kernel spill 64 registers (FP32 K, n = 20011, d = 256: 843 ->
-    // 1057 us)
     if (FULL && bi != bj)
-        epilogue<OUT, true, 2, false>(e, acc, m0, n0, false, wr, wc, lane, T, lds.rn, lds.rs);
+        epilogue<OUT, true, 2>(e, acc, m0, n0, false, wr, wc, lane, T, lds.rn, lds.rs);
     else
-        epilogue<OUT, false, 2, false>(e, acc, m0, n0, bi == bj, wr, wc, lane, T, lds.rn, lds.rs);
+        epilogue<OUT, false, 2>(e, acc, m0, n0, bi == bj, wr, wc, lane, T, lds.rn, lds.rs);
 }
 
 }  // namespace

@@ -36,7 +36,7 @@ __global__ __launch_bounds__(256) void split_stats(const float *X, int64_t n, in
 }
 
 template <typename OUT, bool FULL>
-__global__ __launch_bounds__(GTHREADS, 3) void gram_split_mfma(SplitTile x, Epi e, TileOrder o) {
+__global__ __launch_bounds__(GTHREADS, 2) void gram_split_mfma(SplitTile x, Epi e, TileOrder o) {
     __shared__ __attribute__((aligned(1024))) SplitLds lds;
     int64_t bi, bj;
     if (!tile_of_block(o, bi, bj)) return;
@@ -61,10 +61,16 @@ size_t split_bytes(int64_t n, int64_t d) {
 
 // Below about 3500 points a tile per CU or two is all there is, and the
 // prologue and the flagged launch cost what the product saves unless rows are
-// long.  FP32 kernel / split, us, linear kernel: n = 2560, d = 64 22 / 25, d =
-// 128 31 / 30, d = 784 123 / 82; n = 3072, d = 64 22 / 26; n = 3584, d = 16 29 /
-// 28, d = 64 35 / 31; n = 60000, d = 16 2972 / 2324, d = 784 25772 / 15773.
-bool split_pays(int64_t n, int64_t d) { return n >= 3584 || (n >= 2304 && d > 64); }
+// long; rows of less than half a slab are mostly padding, and sums of one or two
+// products gain nothing in exactness.  FP32 kernel / split, us, Gaussian: n =
+// 2304, d = 65 37 / 33, d = 128 35 / 34, d = 784 129 / 90; n = 3584, d = 16 28 / 29,
+// d = 64 34 / 35, d = 128 50 / 45; n = 60000, d = 16 2701 / 2773 (bfloat16 K 2534 /
+// 1831), d = 128 5286 / 4551, d = 784 25530 / 18607.
+bool split_pays(int64_t n, int64_t d) { return d >= 16 && split_room(n, d); }
+
+// The workspace has room for it for shorter rows too: its size is what it was
+// when they took the split.
+bool split_room(int64_t n, int64_t d) { return n >= 3584 || (n >= 2304 && d > 64); }
 
 kkm_status launch_gram_split(int32_t k_store, bool full, const F32Tile &a, const TileOrder &order,
                              unsigned char *Xs, float *nrm, int32_t *flag, hipStream_t stream) {

@@ -1214,6 +1214,7 @@ void launch_gram_f32_flagged(int32_t k_store, bool full, const F32Tile &a, const
 // the bytes of the split matrix (16-byte aligned), and prologue, product and
 // the flagged FP32 kernel.
 bool split_pays(int64_t n, int64_t d);
+bool split_room(int64_t n, int64_t d);  // products whose workspace has room for it
 size_t split_bytes(int64_t n, int64_t d);
 kkm_status launch_gram_split(int32_t k_store, bool full, const F32Tile &a, const TileOrder &order,
                              unsigned char *Xs, float *nrm, int32_t *flag, hipStream_t stream);

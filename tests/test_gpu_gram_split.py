@@ -117,3 +117,44 @@ def test_batched_takes_a_workspace_without_it(kkm):
     assert torch.equal(r["labels"][2311:], s["labels"][2311:])
     assert r["objective"][1] == s["objective"][1]
     assert abs(r["objective"][0] - s["objective"][0]) <= 1e-5 * abs(s["objective"][0])
+
+
+def _sparse(n, d, kind):
+    import torch
+    g = torch.Generator(device="cuda")
+    g.manual_seed(d)
+    X = torch.randn(n, d, generator=g, device="cuda")
+    if kind == "one feature":
+        Y = torch.zeros_like(X)
+        Y[:, d // 2] = X[:, d // 2]
+        return Y
+    if kind == "three features":
+        Y = torch.zeros_like(X)
+        Y[:, ::d // 3] = X[:, ::d // 3]
+        return Y
+    if kind == "a fifth":
+        return X * (torch.rand(n, d, generator=g, device="cuda") < 0.2)
+    if kind == "a fifth, positive":
+        return X.abs() * (torch.rand(n, d, generator=g, device="cuda") < 0.2)
+    return X
+
+
+@pytest.mark.parametrize("kind", ["one feature", "three features", "a fifth", "a fifth, positive", "dense"])
+@pytest.mark.parametrize("d", [16, 65, 128, 784])
+def test_no_further_off_than_the_fp32_kernel(kkm, d, kind):
+    """Points too few for the split take the FP32 kernel: among the same points,
+    the split's error is no larger, nor is a single product's (rounded once)."""
+    n, few = 3600, 2200
+    X = _sparse(n, d, kind)
+    Xd = X.double()
+    print("split error", d, kind, flush=True)
+    K = kkm.kkm_gram(X, kernel=kkm.LINEAR)[0][:few, :few].double()
+    R = kkm.kkm_gram(X[:few], kernel=kkm.LINEAR)[0].double()
+    want = Xd[:few] @ Xd[:few].T
+    # where both round every entry once, their few different last bits leave the
+    # norm of some 10^6 errors the same within 1%
+    assert float((K - want).norm()) <= 1.01 * float((R - want).norm())
+    if kind == "one feature":
+        # h h' exact, seven roundings of at most 2^-23 of the others' sum (below 2^-6),
+        # l l' below 2^-33, and one rounding of the whole
+        assert bool(((K - want).abs() <= (2.0 ** -24 + 7 * 2.0 ** -29 + 2.0 ** -33) * want.abs()).all())
