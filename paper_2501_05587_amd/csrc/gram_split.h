@@ -86,19 +86,17 @@ __device__ __forceinline__ void split_chunk(const float *x, int64_t d, int64_t k
     *reinterpret_cast<bf16x8 *>(dst + 2 * SPP) = l;
 }
 
-// Whether a row (one whole wave) has a value outside the split's range: not
-// finite or above 2^60, or all of a row that is not zero below 2^-40.  Within
-// it no part that counts is subnormal.
+// Whether a row (one whole wave) has a value outside the split's range: neither
+// zero nor between 2^-45 and 2^50 in size, or not finite.  Within it the parts
+// hold every bit, no product or sum that counts is subnormal, and no sum of
+// fewer than 2^27 features overflows.
 __device__ __forceinline__ bool split_row_bad(const float *x, int64_t d, int lane) {
-    float big = 0.f;
     bool bad = false;
     for (int64_t k = lane; k < d; k += kWave) {
         const float v = fabsf(x[k]);
-        bad |= !(v <= 0x1p60f);
-        big = fmaxf(big, v);
+        bad |= !(v == 0.f || (v >= 0x1p-45f && v <= 0x1p50f));
     }
-    big = wave_max(big);
-    return __ballot(bad) != 0 || (big > 0.f && big < 0x1p-40f);
+    return __ballot(bad) != 0;
 }
 
 // One 128 x 128 tile (bi, bj) and its epilogue.  FULL: tiles below the diagonal

@@ -158,3 +158,21 @@ def test_no_further_off_than_the_fp32_kernel(kkm, d, kind):
         # h h' exact, seven roundings of at most 2^-23 of the others' sum (below 2^-6),
         # l l' below 2^-33, and one rounding of the whole
         assert bool(((K - want).abs() <= (2.0 ** -24 + 7 * 2.0 ** -29 + 2.0 ** -33) * want.abs()).all())
+
+
+@pytest.mark.parametrize("full", [False, True])
+def test_a_small_value_beside_a_large_one(kkm, full):
+    """Rows that meet only in a feature where one of them is tiny and the other
+    large: the product keeps the tiny value's last bits."""
+    import torch
+    n, d = 2304, 70
+    g = torch.Generator(device="cuda")
+    g.manual_seed(11)
+    X = torch.zeros(n, d, device="cuda")
+    X[::2, 0] = (1 + torch.rand(n // 2, generator=g, device="cuda")) * 2.0 ** -115
+    X[::2, 1] = 1.0
+    X[1::2, 0] = (1 + torch.rand(n // 2, generator=g, device="cuda")) * 2.0 ** 49
+    print("split small values", full, flush=True)
+    K = kkm.kkm_gram(X, kernel=kkm.LINEAR, shape=kkm.GRAM_FULL if full else kkm.GRAM_TRIANGLE)[0][::2, 1::2].double()
+    want = X[::2, :1].double() @ X[1::2, :1].double().T
+    assert bool(((K - want).abs() <= 2.0 ** -24 * want).all())
