@@ -74,18 +74,27 @@ typedef enum { KKM_EMPTY_INF = 0, KKM_EMPTY_ZERO_CENTROID = 1 } kkm_empty_policy
  *   X       [n, ldx] float32 points, row-major (d features used per row).
  *   n, d    number of points (>= 1) and features (>= 1); ldx >= d.
  *   kernel_type, gamma, coef0, degree   kernel function (see above).
- *   gram_prec  arithmetic of the product: KKM_F32 (FP32 MFMA), KKM_BF16
- *           (inputs rounded to bfloat16, FP32 accumulation) or
+ *   gram_prec  arithmetic of the product: KKM_F32 (FP32 inputs and sums),
+ *           KKM_BF16 (inputs rounded to bfloat16, FP32 accumulation) or
  *           KKM_FP8_ROWSCALED (each row scaled by max|x|/448 and rounded to
  *           OCP FP8 E4M3, FP32 accumulation).  Squared norms for the Gaussian
  *           are taken from the same rounded values the product uses.
+ *           A KKM_F32 product runs on the FP32 matrix unit or, for d >= 16 and
+ *           n >= 3584 (n >= 2304 where d > 64), on the bfloat16 one with every
+ *           value as the sum of three bfloat16 parts that hold all its bits
+ *           (error against 64 bits no larger).  Values that are neither zero
+ *           nor between 2^-45 and 2^50 in size, or not finite, leave the tiles
+ *           of their rows (128 x 128) to the FP32 unit.  The choice depends on
+ *           n, d and X alone, so every entry point and shape gives the same K
+ *           bit for bit, whatever the workspace.
  *   k_store element type of K: KKM_F32 or KKM_BF16.
  *   K       [n, ldk] output, ldk >= n; both triangles are written and K is
  *           exactly symmetric.  With KKM_F32 storage, ldk*4 bytes per row.
  *   diagK   [n] float32 output, K_ii (exactly 1 for the Gaussian).
  *   ws, ws_bytes  device workspace of at least
  *           kkm_gram_workspace_bytes(n, d, gram_prec) bytes (may be NULL
- *           when that is 0).
+ *           when that is 0).  With KKM_F32, 4 n bytes rounded up to 256 are
+ *           accepted: the same K, for large n up to a quarter slower.
  * Errors: KKM_ERR_ARG for bad sizes/params/NULL outputs, KKM_ERR_NOMEM for a
  * small workspace, KKM_ERR_UNSUPPORTED for an unimplemented precision pair.
  */
@@ -288,7 +297,9 @@ size_t kkm_fit_batched_workspace_bytes(const kkm_instance *inst, int32_t count,
  *   times_ms      host double [3], nullable: {Gram with its prologue, all
  *                 steps, final objective pass} on the stream.
  *   ws, ws_bytes  workspace of kkm_fit_batched_workspace_bytes bytes, or
- *                 NULL to let the call allocate (and free) it.
+ *                 NULL to let the call allocate (and free) it.  With KKM_F32
+ *                 products a workspace without the room for their rows' parts
+ *                 (all past the rest) is accepted, with the same results.
  * Synchronises the stream before returning.  KKM_ERR_LABEL names the first
  * problem whose labels0 holds a label outside [0, k); KKM_ERR_NONFINITE is
  * returned when any problem's diag(K) is not finite.
@@ -369,7 +380,8 @@ kkm_status kkm_mlp_train(float *params, float *adam_m, float *adam_v, int64_t d,
  * the gradient and an Adam step (step numbers t0+1 .. t0+steps).  Over all
  * steps the network sees steps * B(B-1)/2 distinct kernel-value pairs.
  * loss_trace: device double [steps].  Asynchronous.  Workspace: at least
- * kkm_mlp_train_fresh_workspace_bytes(B, d, h1, h2, out). */
+ * kkm_mlp_train_fresh_workspace_bytes(B, d, h1, h2, out); the part of it that
+ * kkm_gram can do without may be missing here too. */
 kkm_status kkm_mlp_train_fresh(float *params, float *adam_m, float *adam_v, int64_t d, int64_t h1,
                                int64_t h2, int64_t out, const float *Xtrain, int64_t ldx,
                                int64_t B, int32_t steps, int32_t t0, int32_t kernel_type,

@@ -48,18 +48,16 @@ enum : int32_t { ST_LIVE = 0, ST_CONVERGED = 1, ST_FINAL = 2, ST_DONE = 3, ST_BA
 struct RowSrc {
     const float *X;
     int64_t ldx, d, dpad;
-    unsigned char *Xq;  // [n][dpad] elements of the product's type, or null
+    // [n][dpad] elements of the product's type; FP32: the split rows, null where
+    // the product is not split or splits them itself
+    unsigned char *Xq;
     float *nrm, *scale;
-    unsigned char *Xs;  // FP32 product by split bfloat16, or null
-    int64_t groups;     // its row groups
-    int32_t *flag;
 };
 
 // Product view of one problem (only the member of its precision is used).
 struct GramSrc {
     F32Tile f;
-    LowpTile q;
-    SplitTile s;  // in the place of f where Xs is set and its flag is not
+    LowpTile q;  // FP32: Xq are the split rows, as in RowSrc
 };
 
 // ---------------------------------------------------------------- 1. prologue
@@ -72,18 +70,24 @@ __global__ __launch_bounds__(256) void batch_prologue(const RowSrc *tab, const i
     if (row >= uniform_load(row_start + count)) return;
     const int32_t b = find_inst(row_start, count, row);
     const RowSrc r = uniform_load(tab + b);
-    const int64_t i = row - uniform_load(row_start + b);
+    const int64_t first = uniform_load(row_start + b);
+    const int64_t i = row - first;
     const int lane = threadIdx.x & 63;
     if constexpr (PREC == KKM_F32) {
         const float *x = r.X + i * r.ldx;
-        sqnorm_row(x, r.d, r.nrm + i, lane);
-        if (r.Xs) {
+        const int64_t n = uniform_load(row_start + b + 1) - first;
+        if (split_pays(n, r.d))
+            split_row_stats(x, r.d, true, r.nrm + i, lane);
+        else
+            sqnorm_row(x, r.d, r.nrm + i, lane);
+        if (r.Xq) {
             // rows past n of the last group stay unwritten: they reach no output
-            const int rr = (int)(i % SPG);
-            unsigned char *dst = r.Xs + (i / SPG) * SPB + rr * 64;
-            for (int64_t c = lane; c < 4 * split_slabs(r.d); c += kWave)
-                split_chunk(x, r.d, 8 * c, true, dst + (c >> 2) * r.groups * SPB + (((c & 3) ^ ((rr >> 2) & 3)) * 16));
-            if (split_row_bad(x, r.d, lane) && lane == 0) atomicOr(r.flag, 1);
+            unsigned char *dst = r.Xq + (i / SPG) * SPB;
+            for (int64_t c = lane; c < 4 * split_slabs(r.d); c += kWave) {
+                float v[8];
+                split_load(x, r.d, 8 * c, v);
+                split_store(v, r.d, 8 * c, true, dst + (c >> 2) * split_groups(n) * SPB + split_at((int)(i % SPG), c & 3));
+            }
         }
     } else {
         const int64_t eb = (PREC == KKM_BF16) ? 2 : 1;
@@ -94,21 +98,16 @@ __global__ __launch_bounds__(256) void batch_prologue(const RowSrc *tab, const i
 
 // ---------------------------------------------------------------- 2. Gram
 
-union BatchF32Lds {
-    F32Lds f;
-    SplitLds s;
-};
-
 // Persistent: every workgroup pops chunks of kQueueChunk tiles until the
 // counter passes the tile total, so every wave reaches the exit.  Two
 // workgroups per CU, double-buffered slabs (the persistent loop keeps more
 // state live than the single-problem kernel, which fits three).
-template <int PREC, typename OUT>
+template <int PREC, typename OUT, bool PRE = true>
 __global__ __launch_bounds__(GTHREADS, 2) void batch_gram(const GramSrc *tab,
                                                           const int64_t *tile_start,
                                                           int32_t count,
                                                           unsigned long long *queue) {
-    __shared__ __attribute__((aligned(1024))) std::conditional_t<PREC == KKM_F32, BatchF32Lds, LowpLds<true>> lds;
+    __shared__ __attribute__((aligned(1024))) std::conditional_t<PREC == KKM_F32, SplitOrF32Lds, LowpLds<true>> lds;
     __shared__ long long next;
     const int64_t total = uniform_load(tile_start + count);
     for (;;) {
@@ -123,11 +122,11 @@ __global__ __launch_bounds__(GTHREADS, 2) void batch_gram(const GramSrc *tab,
             int64_t bi, bj;
             tile_coords(t - uniform_load(tile_start + b), bi, bj);
             if constexpr (PREC == KKM_F32) {
-                const SplitTile x = uniform_load(&tab[b].s);
-                if (x.Xs && uniform_load(x.flag) == 0)
-                    split_tile<OUT>(x, uniform_load(&tab[b].f.e), bi, bj, lds.s);
+                const F32Tile f = uniform_load(&tab[b].f);
+                if (split_pays(f.e.n, f.d) && !outside_split(f.e, bi * GM, bj * GM))  // uniform
+                    split_tile<OUT, false, PRE>(split_source(uniform_load(&tab[b].q.Xq), f.e.n, f.d), f, bi, bj, lds.s);
                 else
-                    f32_tile<OUT>(uniform_load(&tab[b].f), bi, bj, lds.f);
+                    f32_tile<OUT>(f, bi, bj, lds.f);
             } else
                 lowp_tile<PREC, OUT>(uniform_load(&tab[b].q), bi, bj, lds);
         }
@@ -276,7 +275,7 @@ struct Plan {
     int64_t *tile_start = nullptr, *row_start = nullptr;
     int32_t *status = nullptr, *iters = nullptr, *step = nullptr, *n_live = nullptr;
     int32_t *flag = nullptr;
-    int32_t *split_flags = nullptr;  // per problem: outside the split product's range
+    bool pre = false;  // the split products' rows are laid out beforehand
     double *objective = nullptr, *J = nullptr;
     int64_t *n_changed = nullptr;
     unsigned long long *queue = nullptr;
@@ -380,16 +379,18 @@ void make_plan(const kkm_instance *inst, int32_t count, int32_t gram_prec, int32
     p.n_live = c.take<int32_t>(1);
     p.flag = c.take<int32_t>(1);
     p.queue = c.take<unsigned long long>(1);
-    // FP32 products that the single run splits: last, so that a workspace
-    // without room for them serves the rest
-    p.split_flags = nullptr;
+    // the split rows of the FP32 products that the single run splits: last, so that
+    // a workspace without room for them serves the rest (the products then split
+    // the rows themselves), and begun on multiples of 256, whatever its address
+    p.pre = split && gram_prec == KKM_F32;
     std::vector<unsigned char *> Xs(count, nullptr);
-    if (split && gram_prec == KKM_F32 && (reinterpret_cast<uintptr_t>(base) & 15) == 0) {
-        p.split_flags = c.take<int32_t>((size_t)count);
+    if (p.pre) {
+        (void)c.take<char>(256);
+        const size_t shift = -reinterpret_cast<uintptr_t>(base) & 255;
         for (int32_t b = 0; b < count; ++b)
             if (split_room(inst[b].n, inst[b].d)) {
                 unsigned char *at = c.take<unsigned char>(split_bytes(inst[b].n, inst[b].d));
-                if (split_pays(inst[b].n, inst[b].d)) Xs[b] = at;
+                if (at && split_pays(inst[b].n, inst[b].d)) Xs[b] = at + shift;
             }
     }
     p.bytes = c.bytes();
@@ -445,12 +446,9 @@ void make_plan(const kkm_instance *inst, int32_t count, int32_t gram_prec, int32
         r.ldx = q.ldx;
         r.d = q.d;
         r.dpad = (gram_prec == KKM_F32) ? q.d : padded_d(q.d, gram_prec);
-        r.Xq = Xq[b];
+        r.Xq = gram_prec == KKM_F32 ? Xs[b] : Xq[b];
         r.nrm = nrm + row_off[b];
         r.scale = scale + row_off[b];
-        r.Xs = Xs[b];
-        r.groups = split_groups(q.n);
-        r.flag = p.split_flags ? p.split_flags + b : nullptr;
     }
     for (int32_t rnk = 0; rnk < count; ++rnk) {
         const int32_t b = order[rnk];
@@ -476,8 +474,7 @@ void make_plan(const kkm_instance *inst, int32_t count, int32_t gram_prec, int32
         g.f.ldx = q.ldx;
         g.f.vec_x = ((q.ldx % 4) == 0) && ((reinterpret_cast<uintptr_t>(q.X) & 15) == 0);
         g.f.e = e;
-        g.s = SplitTile{Xs[b], split_groups(q.n) * SPB, split_slabs(q.d), p.h_rtab[b].flag};
-        g.q.Xq = Xq[b];
+        g.q.Xq = p.h_rtab[b].Xq;
         g.q.ldq_bytes = p.h_rtab[b].dpad * eb;
         g.q.nslab = g.q.ldq_bytes / SLAB;
         g.q.e = e;
@@ -509,7 +506,6 @@ struct BatchBuffers {
 
 kkm_status launch_prologue(const Plan &p, int32_t gram_prec, hipStream_t s) {
     const dim3 g((unsigned)((p.total_n + 3) / 4)), b(256);
-    if (p.split_flags) fill_i32(p.split_flags, p.count, 0, s);
     if (gram_prec == KKM_F32)
         hipLaunchKernelGGL(batch_prologue<KKM_F32>, g, b, 0, s, p.rtab, p.row_start, p.count);
     else if (gram_prec == KKM_BF16)
@@ -529,10 +525,14 @@ kkm_status launch_gram(const Plan &p, int32_t gram_prec, int32_t k_store, int cu
     const dim3 g((unsigned)std::max<int64_t>(1, std::min<int64_t>(want, (int64_t)cus * 2)));
     const dim3 b(GTHREADS);
     const TimedSpan span = timing_begin(TK_GRAM, s);
-    if (gram_prec == KKM_F32 && k_store == KKM_F32)
+    if (gram_prec == KKM_F32 && k_store == KKM_F32 && p.pre)
         hipLaunchKernelGGL((batch_gram<KKM_F32, float>), g, b, 0, s, p.gtab, p.tile_start, p.count, p.queue);
-    else if (gram_prec == KKM_F32)
+    else if (gram_prec == KKM_F32 && k_store == KKM_F32)
+        hipLaunchKernelGGL((batch_gram<KKM_F32, float, false>), g, b, 0, s, p.gtab, p.tile_start, p.count, p.queue);
+    else if (gram_prec == KKM_F32 && p.pre)
         hipLaunchKernelGGL((batch_gram<KKM_F32, uint16_t>), g, b, 0, s, p.gtab, p.tile_start, p.count, p.queue);
+    else if (gram_prec == KKM_F32)
+        hipLaunchKernelGGL((batch_gram<KKM_F32, uint16_t, false>), g, b, 0, s, p.gtab, p.tile_start, p.count, p.queue);
     else if (gram_prec == KKM_BF16 && k_store == KKM_F32)
         hipLaunchKernelGGL((batch_gram<KKM_BF16, float>), g, b, 0, s, p.gtab, p.tile_start, p.count, p.queue);
     else if (gram_prec == KKM_BF16)
@@ -591,10 +591,9 @@ extern "C" kkm_status kkm_fit_batched(const kkm_instance *inst, int32_t count, i
     }
     BatchBuffers bb;
     bb.stream = s;
-    // a workspace without room for the split (or not aligned for it) serves the
-    // FP32 product
+    // a workspace without room for the split rows has the products split them
     bool split = true;
-    if (ws && (ws_bytes < p.bytes || (reinterpret_cast<uintptr_t>(ws) & 15) != 0)) {
+    if (ws && ws_bytes < p.bytes) {
         split = false;
         make_plan(inst, count, gram_prec, k_store, empty_policy, nullptr, p, split);
     }
@@ -606,7 +605,7 @@ extern "C" kkm_status kkm_fit_batched(const kkm_instance *inst, int32_t count, i
         }
     } else {
         hipError_t e = hipMalloc(&bb.ws_own, p.bytes);
-        if (e != hipSuccess && gram_prec == KKM_F32) {  // without the split it may fit
+        if (e != hipSuccess && gram_prec == KKM_F32) {  // without room for the split rows it may fit
             (void)hipGetLastError();
             split = false;
             make_plan(inst, count, gram_prec, k_store, empty_policy, nullptr, p, split);

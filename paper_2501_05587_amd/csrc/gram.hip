@@ -14,7 +14,7 @@
 //
 // Arithmetic of the product (gram_prec):
 //   F32   FP32 inputs, v_mfma_f32_32x32x2_f32, or each input as three
-//         bfloat16 parts and six v_mfma_f32_32x32x16_bf16 (gram_split.h).
+//         bfloat16 parts and eight v_mfma_f32_32x32x16_bf16 (gram_split.h).
 //   BF16  inputs rounded to bfloat16 (round to nearest even), FP32 accumulation,
 //         v_mfma_f32_32x32x16_bf16.
 //   FP8   each row scaled by s_i = max_l |x_il| / 448 and rounded to OCP FP8
@@ -69,8 +69,7 @@ size_t gram_workspace_bytes(int64_t n, int64_t d, int32_t gram_prec, bool split)
     Carver c(nullptr);
     c.take<float>((size_t)n);  // squared norms
     if (gram_prec == KKM_F32 && split && split_room(n, d)) {
-        c.take<int32_t>(1);  // flag: values left to the FP32 kernel
-        c.take<unsigned char>(split_bytes(n, d));
+        c.take<char>(256 + split_bytes(n, d));  // begun on a multiple of 256, whatever the workspace's address
     }
     if (gram_prec != KKM_F32) {
         c.take<float>((size_t)n);  // row scales
@@ -87,12 +86,9 @@ kkm_status gram_launch(const float *X, int64_t n, int64_t d, int64_t ldx, int32_
     const bool full = (shape == KKM_GRAM_FULL);
     Carver c(ws);
     float *nrm = c.take<float>((size_t)n);
-    // a workspace without room for the split (or not aligned for it) is
-    // enough for the FP32 kernel
-    const size_t all = gram_workspace_bytes(n, d, gram_prec);
-    const bool split = gram_prec == KKM_F32 && split_pays(n, d) && ws_bytes >= all &&
-                       (reinterpret_cast<uintptr_t>(ws) & 15) == 0;
-    const size_t need = split ? all : gram_workspace_bytes(n, d, gram_prec, false);
+    const bool split = gram_prec == KKM_F32 && split_pays(n, d);
+    // a workspace without room for the split rows has the product split them
+    const size_t need = gram_workspace_bytes(n, d, gram_prec, false);
     if (ws == nullptr || ws_bytes < need) {
         set_error("kkm_gram: workspace of %zu bytes is smaller than %zu", ws_bytes, need);
         return KKM_ERR_NOMEM;
@@ -152,9 +148,10 @@ kkm_status gram_launch(const float *X, int64_t n, int64_t d, int64_t ldx, int32_
         a.vec_x = ((ldx % 4) == 0) && ((reinterpret_cast<uintptr_t>(X) & 15) == 0);
         a.e = e;
         if (split) {
-            int32_t *flag = c.take<int32_t>(1);
-            unsigned char *Xs = c.take<unsigned char>(split_bytes(n, d));
-            return launch_gram_split(k_store, full, a, order, Xs, nrm, flag, stream);
+            const uintptr_t at = reinterpret_cast<uintptr_t>(c.take<char>(256 + split_bytes(n, d)));
+            unsigned char *Xs = reinterpret_cast<unsigned char *>((at + 255) & ~uintptr_t(255));
+            if (ws_bytes < gram_workspace_bytes(n, d, gram_prec)) Xs = nullptr;
+            return launch_gram_split(k_store, full, a, order, Xs, nrm, stream);
         }
         const TimedSpan span = timing_begin(TK_GRAM, stream);
         launch_gram_f32(k_store, full, dim3((unsigned)grid), a, order, stream);

@@ -16,32 +16,7 @@ __global__ __launch_bounds__(GTHREADS, 2) void gram_f32_mfma(F32Tile a, TileOrde
     f32_tile<OUT, FULL>(a, bi, bj, lds);
 }
 
-// The values that the split product leaves to this one.
-template <typename OUT, bool FULL>
-__global__ __launch_bounds__(GTHREADS, 2) void gram_f32_flagged(F32Tile a, TileOrder o, const int32_t *flag) {
-    __shared__ __attribute__((aligned(16))) F32Lds lds;
-    if (*flag == 0) return;
-    for (int64_t pid = blockIdx.x; pid < o.per_xcd * 8; pid += gridDim.x) {
-        int64_t bi, bj;
-        if (tile_of_block(o, pid, bi, bj)) f32_tile<OUT, FULL>(a, bi, bj, lds);  // uniform
-    }
-}
-
 }  // namespace
-
-void launch_gram_f32_flagged(int32_t k_store, bool full, const F32Tile &a, const TileOrder &order,
-                             const int32_t *flag, hipStream_t stream) {
-    // two workgroups per CU; a multiple of 8, so that each keeps to its XCD's tiles
-    const dim3 g((unsigned)(order.per_xcd < 64 ? order.per_xcd * 8 : 512)), b(GTHREADS);
-    if (k_store == KKM_F32 && !full)
-        hipLaunchKernelGGL((gram_f32_flagged<float, false>), g, b, 0, stream, a, order, flag);
-    else if (k_store == KKM_F32)
-        hipLaunchKernelGGL((gram_f32_flagged<float, true>), g, b, 0, stream, a, order, flag);
-    else if (!full)
-        hipLaunchKernelGGL((gram_f32_flagged<uint16_t, false>), g, b, 0, stream, a, order, flag);
-    else
-        hipLaunchKernelGGL((gram_f32_flagged<uint16_t, true>), g, b, 0, stream, a, order, flag);
-}
 
 void launch_gram_f32(int32_t k_store, bool full, dim3 g, const F32Tile &a, const TileOrder &order,
                      hipStream_t stream) {

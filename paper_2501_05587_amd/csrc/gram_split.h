@@ -25,9 +25,13 @@
 // rate that a plain bfloat16 product of 8192^3 reaches on this card (1.13).
 //
 // Values whose low parts would leave the bfloat16 range, and infinities and
-// NaNs (inf - inf inside a split), are left to the FP32 kernel: the prologue
-// raises a flag on the device, this kernel then returns at once and the FP32
-// kernel, launched behind it, does the work; without the flag that one returns.
+// NaNs (inf - inf inside a split), are left to the FP32 unit: the prologue marks
+// their rows in the sign of the squared norm, and a tile with a marked row is the
+// FP32 kernel's tile.
+//
+// The parts are laid out once (PRE) where the workspace has room for them, else
+// split while they are staged: the same parts, so the same K bit for bit (n =
+// 60000, d = 784 18.8 / 22.2 ms, d = 128 4.7 / 5.2; n = 3584, d = 128 43 / 42 us).
 //
 // Per 32-feature slab a 128 x 128 tile stages 2 x 24 KiB with direct
 // global-to-LDS loads, already in LDS order (the prologue wrote them so), single
@@ -59,23 +63,34 @@ struct SplitLds {
 
 // A matrix split and laid out: Xs [slab][group][plane][16 rows x 64 bytes].
 struct SplitTile {
-    const unsigned char *Xs;  // null: not split
+    const unsigned char *Xs;
     int64_t slab_bytes;       // groups * SPB
     int64_t nslab;
-    const int32_t *flag;      // set: a value is outside the split's range
+};
+
+union SplitOrF32Lds {
+    SplitLds s;
+    F32Lds f;
 };
 
 __host__ __device__ inline int64_t split_groups(int64_t n) { return (n + GM - 1) / GM * (GM / SPG); }
 __host__ __device__ inline int64_t split_slabs(int64_t d) { return (d + SPK - 1) / SPK; }
+__host__ __device__ inline SplitTile split_source(const unsigned char *Xs, int64_t n, int64_t d) {
+    return SplitTile{Xs, split_groups(n) * SPB, split_slabs(d)};
+}
 
-// The three parts of features k0 .. k0+7 of a row x (zeros past d, or all
-// zeros if !in), 16 bytes each, SPP apart.
-__device__ __forceinline__ void split_chunk(const float *x, int64_t d, int64_t k0, bool in, unsigned char *dst) {
+// Where chunk c of row r (of 128) of a tile operand's slab sits.
+__device__ __forceinline__ int split_at(int r, int c) {
+    return (r / SPG) * SPB + (r % SPG) * (SPK * 2) + ((c ^ ((r >> 2) & 3)) * 16);
+}
+
+// The three parts of the eight features k0 .. k0+7 of a row, x (zeros past d, or
+// all zeros if !in), 16 bytes each, SPP apart.
+__device__ __forceinline__ void split_store(const float (&x)[8], int64_t d, int64_t k0, bool in, unsigned char *dst) {
     bf16x8 h, m, l;
 #pragma unroll
     for (int u = 0; u < 8; ++u) {
-        const float a = x[min(k0 + u, d - 1)];
-        const float v = (in && k0 + u < d) ? a : 0.f;
+        const float v = (in && k0 + u < d) ? x[u] : 0.f;
         h[u] = (__bf16)v;
         const float v1 = v - (float)h[u];
         m[u] = (__bf16)v1;
@@ -84,6 +99,10 @@ __device__ __forceinline__ void split_chunk(const float *x, int64_t d, int64_t k
     *reinterpret_cast<bf16x8 *>(dst) = h;
     *reinterpret_cast<bf16x8 *>(dst + SPP) = m;
     *reinterpret_cast<bf16x8 *>(dst + 2 * SPP) = l;
+}
+__device__ __forceinline__ void split_load(const float *x, int64_t d, int64_t k0, float (&v)[8]) {
+#pragma unroll
+    for (int u = 0; u < 8; ++u) v[u] = x[min(k0 + u, d - 1)];
 }
 
 // Whether a row (one whole wave) has a value outside the split's range: neither
@@ -99,10 +118,30 @@ __device__ __forceinline__ bool split_row_bad(const float *x, int64_t d, int lan
     return __ballot(bad) != 0;
 }
 
+// A row's squared norm (or 0) and, in its sign, whether the row is outside the
+// split's range, by one whole wave.
+__device__ __forceinline__ void split_row_stats(const float *x, int64_t d, bool norm, float *nrm, int lane) {
+    float s = 0.f;
+    if (norm) sqnorm_row(x, d, &s, lane);  // lane 0's
+    const bool bad = split_row_bad(x, d, lane);
+    if (lane == 0) *nrm = bad ? __uint_as_float(__float_as_uint(s) | 0x80000000u) : fabsf(s);
+}
+
+// Whether the tile (rows m0.., columns n0..) has a row outside the split's
+// range (the whole workgroup calls).
+__device__ __forceinline__ bool outside_split(const Epi &e, int64_t m0, int64_t n0) {
+    const int t = threadIdx.x;
+    const int64_t g = (t < GM) ? m0 + t : n0 + (t - GM);
+    return __syncthreads_or(g < e.n && (__float_as_uint(e.nrm[g]) >> 31) != 0) != 0;
+}
+
 // One 128 x 128 tile (bi, bj) and its epilogue.  FULL: tiles below the diagonal
 // swap the order of mixed terms, so they round as their mirror above does.
-template <typename OUT, bool FULL = false>
-__device__ __forceinline__ void split_tile(const SplitTile &x, const Epi &e, int64_t bi, int64_t bj, SplitLds &lds) {
+// !PRE: the rows are split as they are staged.
+template <typename OUT, bool FULL, bool PRE>
+__device__ __forceinline__ void split_tile(const SplitTile &x, const F32Tile &src, int64_t bi, int64_t bj,
+                                           SplitLds &lds) {
+    const Epi &e = src.e;
     const int64_t m0 = bi * GM, n0 = bj * GM;
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -115,7 +154,41 @@ __device__ __forceinline__ void split_tile(const SplitTile &x, const Epi &e, int
     const unsigned char *gb = x.Xs + bj * SPT + wave * Q + lane * 16;
     typedef __attribute__((address_space(3))) void lds_void;
     typedef const __attribute__((address_space(1))) void glb_void;
-    auto fetch = [&]() {
+    auto fetch = [&](int64_t kt) {
+        if constexpr (!PRE) {
+            // two chunks of 8 features of each operand per thread, all their loads in flight
+            float v[2][2][8];
+            const int64_t k0 = kt * SPK + 8 * (tid & 3);
+            auto load = [&](auto vec) {
+#pragma unroll
+                for (int o = 0; o < 2; ++o)
+#pragma unroll
+                    for (int u = 0; u < 2; ++u) {
+                        const int64_t row = (o ? n0 : m0) + (tid >> 2) + 64 * u;
+                        const float *p = src.X + min(row, e.n - 1) * src.ldx;
+                        if constexpr (decltype(vec)::value) {
+                            const f32x4 q0 = *reinterpret_cast<const f32x4 *>(p + k0);
+                            const f32x4 q1 = *reinterpret_cast<const f32x4 *>(p + k0 + 4);
+#pragma unroll
+                            for (int c = 0; c < 4; ++c) v[o][u][c] = q0[c], v[o][u][4 + c] = q1[c];
+                        } else {
+                            split_load(p, src.d, k0, v[o][u]);
+                        }
+                    }
+            };
+            if (src.vec_x && (kt + 1) * SPK <= src.d)  // uniform
+                load(std::true_type{});
+            else
+                load(std::false_type{});
+#pragma unroll
+            for (int o = 0; o < 2; ++o)
+#pragma unroll
+                for (int u = 0; u < 2; ++u) {
+                    const int r = (tid >> 2) + 64 * u;
+                    split_store(v[o][u], src.d, k0, (o ? n0 : m0) + r < e.n, lds.op[o] + split_at(r, tid & 3));
+                }
+            return;
+        }
 #pragma unroll
         for (int b = 0; b < NB; ++b)
             __builtin_amdgcn_global_load_lds((glb_void *)(ga + b * 1024), (lds_void *)(&lds.op[0][wave * Q + b * 1024]),
@@ -146,8 +219,8 @@ __device__ __forceinline__ void split_tile(const SplitTile &x, const Epi &e, int
         return *reinterpret_cast<const bf16x8 *>(op + i * (2 * SPB) + p * SPP + chunk);
     };
     for (int64_t kt = 0; kt < x.nslab; ++kt) {
-        fetch();
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        fetch(kt);
+        if constexpr (PRE) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         __syncthreads();
 #pragma unroll
         for (int s = 0; s < 2; ++s) {

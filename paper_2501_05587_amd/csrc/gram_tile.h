@@ -235,7 +235,7 @@ __device__ __forceinline__ void stage_norms(const Epi &e, int64_t m0, int64_t n0
     const int t = threadIdx.x;
     const int64_t g = (t < GM) ? m0 + t : n0 + (t - GM);
     const bool in = g < e.n;
-    rn[t] = (e.kernel == KKM_GAUSS && in) ? e.nrm[g] : 0.f;
+    rn[t] = (e.kernel == KKM_GAUSS && in) ? fabsf(e.nrm[g]) : 0.f;  // its sign: outside_split
     rs[t] = (e.scale && in) ? e.scale[g] : 1.f;
 }
 
@@ -1206,18 +1206,24 @@ __device__ __forceinline__ void quantize_row(const float *x, int64_t d, int64_t 
 // gram_lowp.hip, gram_lowp256.hip); g is the grid of the launch order.
 void launch_gram_f32(int32_t k_store, bool full, dim3 g, const F32Tile &a, const TileOrder &order,
                      hipStream_t stream);
-// The same where *flag is set, nothing else (a fixed number of workgroups walks
-// the tiles).
-void launch_gram_f32_flagged(int32_t k_store, bool full, const F32Tile &a, const TileOrder &order,
-                             const int32_t *flag, hipStream_t stream);
-// The FP32 product by split bfloat16 (gram_split.h): which products take it,
-// the bytes of the split matrix (16-byte aligned), and prologue, product and
-// the flagged FP32 kernel.
-bool split_pays(int64_t n, int64_t d);
-bool split_room(int64_t n, int64_t d);  // products whose workspace has room for it
+
+// Which FP32 products are taken as split bfloat16 (gram_split.h), whatever the
+// workspace.  Below about 3500 points a tile per CU or two is all there is, and
+// the prologue costs what the product saves unless rows are long; rows of less
+// than half a slab are mostly padding, and sums of one or two products gain
+// nothing in exactness.  FP32 kernel / split, us, Gaussian: n = 2304, d = 65 37 /
+// 33, d = 128 35 / 34, d = 784 129 / 90; n = 3584, d = 16 28 / 29, d = 64 34 / 35, d =
+// 128 50 / 45; n = 60000, d = 16 2701 / 2773 (bfloat16 K 2534 / 1831), d = 128 5286 /
+// 4551, d = 784 25530 / 18607.  The workspace's size has room for the split rows
+// of shorter rows too (split_room): it is what it was when they were split.
+__host__ __device__ inline bool split_room(int64_t n, int64_t d) { return n >= 3584 || (n >= 2304 && d > 64); }
+__host__ __device__ inline bool split_pays(int64_t n, int64_t d) { return d >= 16 && split_room(n, d); }
+
+// The bytes of the split rows, and the split product with its prologue; Xs null:
+// the product splits the rows as it stages them, with the same results.
 size_t split_bytes(int64_t n, int64_t d);
 kkm_status launch_gram_split(int32_t k_store, bool full, const F32Tile &a, const TileOrder &order,
-                             unsigned char *Xs, float *nrm, int32_t *flag, hipStream_t stream);
+                             unsigned char *Xs, float *nrm, hipStream_t stream);
 void launch_gram_lowp(int32_t gram_prec, int32_t k_store, bool full, dim3 g, const LowpTile &a,
                       const TileOrder &order, hipStream_t stream);
 void launch_gram_lowp256(int32_t gram_prec, int32_t k_store, dim3 g, const LowpTile &a,

@@ -59,8 +59,8 @@ void flag_nonfinite(const float *v, int64_t n, int32_t *flag, hipStream_t stream
 // p[0..n) = v by a kernel (graph-safe, unlike a memset node).
 void fill_i32(int32_t *p, int64_t n, int32_t v, hipStream_t stream);
 
-// split: with room for the FP32 product by split bfloat16, where it is taken; a
-// launch whose workspace lacks it runs the FP32 kernel.
+// split: with room for the rows of the FP32 product by split bfloat16, where it is
+// taken; a launch whose workspace lacks it splits them as it stages them.
 size_t gram_workspace_bytes(int64_t n, int64_t d, int32_t gram_prec, bool split = true);
 // shape: KKM_GRAM_TRIANGLE (upper-triangle tiles, mirrored stores) or
 // KKM_GRAM_FULL (every tile, each storing its own block).  packed: K in the

@@ -451,7 +451,7 @@ extern "C" kkm_status kkm_mlp_train_fresh(float *params, float *adam_m, float *a
     KKM_TRY(check_kernel(kernel_type, gamma, coef0, degree));
     size_t need = 0;
     TrainWs w = carve_train(ws, m, B, &need);
-    // without room for the split parts of a large batch the FP32 Gram kernel runs
+    // without room for the split rows of a large batch the product splits them
     const size_t least = need + gram_workspace_bytes(B, d, KKM_F32, false);
     if (!ws || ws_bytes < least) {
         set_error("kkm_mlp_train_fresh: workspace of %zu bytes is smaller than %zu", ws_bytes, least);

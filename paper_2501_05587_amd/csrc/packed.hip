@@ -822,7 +822,7 @@ extern "C" kkm_status kkm_fit_packed(const float *X, int64_t n, int64_t d, int64
         c.take<int32_t>(1);        // non-finite flag
         return c.bytes();
     };
-    if (hipMalloc(&block, block_bytes()) != hipSuccess) {  // without the split it may fit
+    if (hipMalloc(&block, block_bytes()) != hipSuccess) {  // without room for the split rows it may fit
         (void)hipGetLastError();
         gws = gram_workspace_bytes(n, d, gram_prec, false);
         KKM_HIP(hipMalloc(&block, block_bytes()));

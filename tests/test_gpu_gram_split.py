@@ -2,8 +2,8 @@
 of three-part values: against 64 bits, in every shape and layout, and against
 the FP32 kernel for the values that are left to it.
 
-A workspace that holds only the row norms selects the FP32 kernel, which the
-split must accept as before.
+A workspace that holds only the row norms is accepted as before: the product
+then splits the rows as it stages them.
 """
 import numpy as np
 import pytest
@@ -176,3 +176,97 @@ def test_a_small_value_beside_a_large_one(kkm, full):
     K = kkm.kkm_gram(X, kernel=kkm.LINEAR, shape=kkm.GRAM_FULL if full else kkm.GRAM_TRIANGLE)[0][::2, 1::2].double()
     want = X[::2, :1].double() @ X[1::2, :1].double().T
     assert bool(((K - want).abs() <= 2.0 ** -24 * want).all())
+
+
+@pytest.mark.parametrize("kernel", ["GAUSS", "POLY"])
+@pytest.mark.parametrize("store", ["F32", "BF16"])
+@pytest.mark.parametrize("n,d,pad,offset", [(2304, 65, 0, 0), (2311, 784, 0, 0), (3600, 31, 0, 0), (3585, 33, 3, 1),
+                                            (3700, 64, 4, 0), (4100, 128, 0, 0), (3600, 15, 0, 0), (3600, 16, 0, 0)])
+def test_the_workspace_does_not_change_k(kkm, n, d, pad, offset, store, kernel):
+    """Rows split beforehand, in a workspace with room for them (16-byte aligned or
+    not), or while they are staged: the same K bit for bit, in every shape."""
+    import torch
+    X = _points(n, d, pad, offset)
+    a = dict(kernel=getattr(kkm, kernel), gamma=1.0 / d, coef0=1.0, degree=2, k_store=getattr(kkm, store))
+    print("split workspaces", n, d, pad, store, kernel, flush=True)
+    need = kkm.gram_workspace_bytes(n, d, kkm.F32)
+    K, diag = kkm.kkm_gram(X, **a)
+    for ws in (_small_ws(n), torch.empty(need + 4, dtype=torch.uint8, device="cuda")[4:],
+               torch.empty(need - 1, dtype=torch.uint8, device="cuda")):
+        R, rdiag = kkm.kkm_gram(X, ws=ws, **a)
+        assert torch.equal(K, R) and torch.equal(diag, rdiag)
+    R, rdiag = kkm.kkm_gram(X, ws=_small_ws(n), shape=kkm.GRAM_FULL, **a)
+    assert torch.equal(K, R) and torch.equal(diag, rdiag)
+    P, _ = kkm.kkm_gram_packed(X, **a)
+    R, _ = kkm.kkm_gram_packed(X, ws=_small_ws(n), **a)
+    wide = (-(-n // 1024)) * 1024
+    assert torch.equal(P[:1024 * wide].view(1024, wide)[:, :n], R[:1024 * wide].view(1024, wide)[:, :n])
+
+
+@pytest.mark.parametrize("small", [False, True])
+@pytest.mark.parametrize("full", [False, True])
+@pytest.mark.parametrize("value", [float("inf"), float("nan"), 2.0 ** 51, 2.0 ** -46])
+def test_only_the_tiles_of_marked_rows_leave_the_split(kkm, value, full, small):
+    """A row outside the split's range: the tiles of its 128 rows are the FP32
+    kernel's, the others are what they are without that row."""
+    import torch
+    n, d = 2311, 70
+    X = _points(n, d)
+    Y = X.clone()
+    Y[n - 1, 3] = value
+    a = dict(kernel=kkm.LINEAR, shape=kkm.GRAM_FULL if full else kkm.GRAM_TRIANGLE,
+             ws=_small_ws(n) if small else None)
+    print("split marked rows", value, full, small, flush=True)
+    K = kkm.kkm_gram(Y, **a)[0].clone()
+    last = (n - 1) // 128 * 128
+    assert torch.equal(K[:last, :last], kkm.kkm_gram(X, **a)[0][:last, :last])
+    R = kkm.kkm_gram(Y[1000:], kernel=kkm.LINEAR)[0].contiguous()  # too few for the split
+    bits = lambda t: t.contiguous().view(torch.int32)
+    assert torch.equal(bits(K[last:, 1000:n]), bits(R[last - 1000:n - 1000, :n - 1000]))
+    assert torch.equal(bits(K[1000:n, last:n]), bits(R[:n - 1000, last - 1000:n - 1000]))
+
+
+def test_batched_equals_the_single_runs(kkm):
+    """Problems whose product is split, one of them with rows outside its range, and
+    one too small for it, in one batch, with room for the split rows and without:
+    the single runs' labels and objectives bit for bit."""
+    import torch
+    X = [_points(2311, 96), _points(3601, 20).clone(), _points(500, 20), _points(2400, 70)]
+    X[1][77] *= 2.0 ** -60
+    X[1][3000, 5] = 2.0 ** 55
+    probs = [dict(X=x, k=5, kernel=kkm.POLY, gamma=2.0 ** -60, coef0=1.0, degree=2) for x in X]
+    g = np.random.default_rng(3)
+    ns = [x.shape[0] for x in X]
+    l0 = torch.from_numpy(g.integers(0, 5, sum(ns)).astype(np.int32)).cuda()
+    need = kkm.kkm_fit_batched_workspace_bytes(probs, kkm.F32, kkm.F32)
+    room = 256 + sum(-(-n // 128) * 8 * (-(-x.shape[1] // 32)) * 3072 for n, x in zip(ns, X) if n >= 2304)
+    print("split batch", flush=True)
+    for ws in (None, torch.empty(need - room, dtype=torch.uint8, device="cuda")):
+        r = kkm.kkm_fit_batched(probs, l0, kkm.F32, kkm.F32, max_iter=6, ws=ws)
+        at = 0
+        for b, (n, p) in enumerate(zip(ns, probs)):
+            one = kkm.kkm_fit_ex(p["X"], 5, l0[at:at + n], kernel=kkm.POLY, gamma=2.0 ** -60, coef0=1.0, degree=2,
+                                 max_iter=6)
+            assert torch.equal(r["labels"][at:at + n], one["labels"]), b
+            assert r["objective"][b] == one["objective"] and r["iters"][b] == one["iters"], b
+            at += n
+
+
+def test_fresh_training_with_the_smaller_workspace(kkm):
+    """A large batch's kernel values are split: a workspace without room for the
+    split rows gives the same step."""
+    import torch
+    B, d, net = 2304, 70, dict(h1=40, h2=36, out=20)
+    X = _points(B, d)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(1)
+    th = torch.randn(kkm.mlp_param_count(d, 40, 36, 20), generator=g, device="cuda") * 0.1
+    need = kkm.lib().kkm_mlp_train_fresh_workspace_bytes(B, d, 40, 36, 20)
+    out = []
+    print("split training", flush=True)
+    for size in (need, need - 256 - -(-B // 128) * 8 * 3 * 3072):
+        p, m, v = th.clone(), torch.zeros_like(th), torch.zeros_like(th)
+        ws = torch.empty(size, dtype=torch.uint8, device="cuda")
+        tr = kkm.kkm_mlp_train_fresh(p, m, v, X, B, kernel=kkm.GAUSS, gamma=1.0 / d, ws=ws, **net)
+        out.append((p, m, v, tr))
+    assert all(torch.equal(a, b) for a, b in zip(*out))
