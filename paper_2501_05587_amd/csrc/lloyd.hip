@@ -551,8 +551,8 @@ __device__ void kpp_sums(double v, int64_t n, const KppSums &q) {
     if (tid == 0) q.gsum[blockIdx.x] = (sh[0] + sh[1]) + (sh[2] + sh[3]);
 }
 
-// One seed: the select of seed t from the last step's sums (every workgroup
-// does it for itself; workgroup 0 records it), then dmin_i = min over seeds
+// One seed: the select of seed t from the last step's sums (SELECT: every
+// workgroup does it for itself; workgroup 0 records it), then dmin_i = min over seeds
 // 0..t of |F_i - F_seed|^2 and the new sums.  `was` and `now` alternate between
 // two sets, so no workgroup overwrites what another still reads.  Wave w of a
 // workgroup takes rows 32w .. 32w+31 of its group, kKppPass at a time with all
@@ -571,13 +571,21 @@ struct KppState {
     KppSums q;
 };
 
-constexpr int kKppThreads = 512;
-constexpr int kKppWaveRows = kKppGroup / (kKppThreads / kWave);
+// Every workgroup's own select reads all the group sums, n / 256 of them n / 256
+// times over a launch, so it pays for few groups; past them the select is a
+// launch of its own again (SELECT false), in front of an update of 256 threads.
+// Per seed, own select / two launches: n = 50000, f = 16 9.9 / 12.9 us, f = 256
+// 14.8 / 16.4; n = 100000 14.3 / 14.3 and 22.8 / 23.7; n = 150000 22 / 16 and 36 / 33;
+// n = 10^6 121 / 51 and 222 / 192; n = 4 10^6, f = 16 1053 / 194.
+constexpr int64_t kKppOwnSelect = 384;  // groups
+template <bool SELECT> constexpr int kpp_threads() { return SELECT ? 512 : 256; }
 
-template <bool VEC>
-__global__ __launch_bounds__(kKppThreads) void kpp_step(const float *F, int64_t n, int64_t f, int64_t ldf,
-                                                int32_t *seeds, int t, int64_t first, double u,
-                                                KppState was, KppState now) {
+template <bool VEC, bool SELECT>
+__global__ __launch_bounds__(kpp_threads<SELECT>()) void kpp_step(const float *F, int64_t n, int64_t f, int64_t ldf,
+                                                                  int32_t *seeds, int t, int64_t first, double u,
+                                                                  KppState was, KppState now) {
+    constexpr int kKppWaveRows = kKppGroup / (kpp_threads<SELECT>() / kWave);
+    constexpr int passes = SELECT ? 1 : kKppWaveRows / kKppPass;  // unrolled
     __shared__ float dist[kKppGroup];
     __shared__ int32_t chosen;
     const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -590,14 +598,16 @@ __global__ __launch_bounds__(kKppThreads) void kpp_step(const float *F, int64_t 
     };
     fetch(0, 0);
     int64_t seed = first;
-    if (t > 0) {
+    if constexpr (SELECT) {
         kpp_select_seed(was.q, was.dmin, n, u, &chosen);
         __syncthreads();
         seed = __builtin_amdgcn_readfirstlane(chosen);
+    } else if (t > 0) {
+        seed = seeds[t];
     }
-    if (blockIdx.x == 0 && threadIdx.x == 0) seeds[t] = (int32_t)seed;
+    if (blockIdx.x == 0 && threadIdx.x == 0 && (SELECT || t == 0)) seeds[t] = (int32_t)seed;
     const float *c = F + seed * ldf;
-#pragma unroll 1
+#pragma unroll passes
     for (int p = 0; p < kKppWaveRows; p += kKppPass) {
         float d[kKppPass];
 #pragma unroll
@@ -785,12 +795,22 @@ extern "C" kkm_status kkm_feature_kmeanspp(const float *F, int64_t n, int64_t f,
     const KppState st[2] = {{dmin, q}, {fn, KppSums{sums2, sums2 + (n + kKppRows - 1) / kKppRows}}};
     for (int32_t t = 0; t + 1 < k; ++t) {
         const KppState &was = st[(t + 1) & 1], &now = st[t & 1];
-        if (vec_ok(F, ldf, f))
-            hipLaunchKernelGGL(kpp_step<true>, dim3((unsigned)ng), dim3(kKppThreads), 0, s, F, n, f, ldf, seeds, t,
+        const bool select = t > 0 && ng <= kKppOwnSelect;
+        if (t > 0 && !select)
+            hipLaunchKernelGGL(kpp_select, dim3(1), dim3(256), 0, s, was.q, was.dmin, n, uniforms[t], seeds + t);
+        auto step = [&](auto vec, auto sel) {
+            constexpr bool V = decltype(vec)::value, S = decltype(sel)::value;
+            hipLaunchKernelGGL((kpp_step<V, S>), dim3((unsigned)ng), dim3(kpp_threads<S>()), 0, s, F, n, f, ldf, seeds, t,
                                first < n ? first : n - 1, uniforms[t], was, now);
+        };
+        if (vec_ok(F, ldf, f) && select)
+            step(std::true_type{}, std::true_type{});
+        else if (vec_ok(F, ldf, f))
+            step(std::true_type{}, std::false_type{});
+        else if (select)
+            step(std::false_type{}, std::true_type{});
         else
-            hipLaunchKernelGGL(kpp_step<false>, dim3((unsigned)ng), dim3(kKppThreads), 0, s, F, n, f, ldf, seeds, t,
-                               first < n ? first : n - 1, uniforms[t], was, now);
+            step(std::false_type{}, std::false_type{});
         KKM_HIP(hipGetLastError());
     }
     if (k > 1) {

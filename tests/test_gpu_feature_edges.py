@@ -72,3 +72,11 @@ def test_seeding_and_lloyd_step(kkm, n, f, k, pad):
     assert changed[0] == (new != lab).sum() and it == 1
     assert abs(J - want) <= (f + n + 3) * 2.0 ** -24 * ((X * X).sum() + 2 * np.abs(X).sum() * np.abs(C).max()
                                                       + n * norms[cnt > 0].max())
+
+
+@pytest.mark.parametrize("n,f,k,pad", [(98304, 5, 3, 0), (98305, 5, 3, 1), (98305, 4, 2, 0), (98560, 300, 2, 0),
+                                       (300001, 3, 4, 0)])
+def test_seeding_either_side_of_its_own_select(kkm, n, f, k, pad):
+    """384 groups of 256 rows are the most that every workgroup selects from for
+    itself; past them a launch selects."""
+    test_seeding_and_lloyd_step(kkm, n, f, k, pad)
