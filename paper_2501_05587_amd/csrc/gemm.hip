@@ -2,7 +2,7 @@
 // and its gradient): 64 x 64 output tile per 256-thread workgroup, 4
 // waves as 2 x 2, each one 32 x 32 MFMA block; k staged in LDS in slabs of 32.
 // BF16 (operands rounded to nearest even): the 32 x 32 tiles of gemm_small.h,
-// or the wide tiles below for a layer forward of many rows.
+// or the wider tiles below for a layer forward of many rows.
 #include "gemm_small.h"
 
 namespace kkm {
@@ -88,28 +88,35 @@ __global__ __launch_bounds__(256) void gemm_f32(GemmArgs g, int epi) {
 // ---------------------------------------------------------------- wide tiles
 //
 // Both operands k-contiguous (A(m,k) = A[m*lda+k], B(n,k) = B[n*ldb+k]) and
-// large: a 64 x 256 output tile per workgroup, wave w owning columns
-// 64w .. 64w+63 as 2 x 2 blocks of 32 x 32.  k-slabs of 64 floats per row are
+// many rows: a 64 x 256 output tile per workgroup, wave w owning columns
+// 64w .. 64w+63 as 2 x 2 blocks of 32 x 32, or for a narrow layer a 64 x 64 tile,
+// a wave owning one block.  k-slabs of 64 floats per row are
 // loaded a slab ahead into registers without branches (behind one each load
 // would be waited for before the next), rounded to bfloat16 and staged in LDS,
 // so a fragment is one 16-byte read.  MFMA s (s = 0, 1) of each 32 k takes
-// k = 16h + 8s .. 16h + 8s + 7 from lane half h.  (32768 x 512 x 512: 98 us
+// k = 16h + 8s .. 16h + 8s + 7 from lane half h; of a narrow layer, k = 16s + 8h ..
+// 16s + 8h + 7, the order of the small tiles.  (32768 x 512 x 512: 98 us
 // with FP32 slabs of 32, rounded per fragment, and branches; 72 us so.)
 
-constexpr int WM = 64, WN = 256, WK = 64, WLD = WK + 8;
+constexpr int WM = 64, WK = 64, WLD = WK + 8;
 
-struct WideLds {
+template <int WN> struct WideLds {
     __bf16 a[WM][WLD];
     __bf16 b[WN][WLD];
 };
 
+template <int WN>
 __global__ __launch_bounds__(256, 2) void gemm_wide(GemmArgs g, bool act, int vec) {
-    __shared__ __attribute__((aligned(16))) WideLds lds;
+    static_assert(WN == 256 || WN == 64, "four waves of 2 x 2 blocks or of one");
+    constexpr bool WIDE = WN == 256;
+    constexpr int NB = WIDE ? 2 : 1;  // blocks a wave owns each way
+    __shared__ __attribute__((aligned(16))) WideLds<WN> lds;
     const int64_t m0 = (int64_t)blockIdx.y * WM, n0 = (int64_t)blockIdx.x * WN;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int half = lane >> 5, l32 = lane & 31;
     const int lr = tid >> 4, lc = (tid & 15) * 4;  // 16 threads x 4 floats per row of a slab
     constexpr int RA = WM / 16, RB = WN / 16;
+    const int wm = WIDE ? 0 : 32 * (wave >> 1), wn = WIDE ? 64 * wave : 32 * (wave & 1);  // the wave's rows and columns
     typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
 
     f32x4 ra[RA], rb[RB];
@@ -139,11 +146,11 @@ __global__ __launch_bounds__(256, 2) void gemm_wide(GemmArgs g, bool act, int ve
                 __builtin_convertvector(mask4(rb[u], k0 + lc, g.K, n0 + lr + 16 * u < g.N), bf16x4);
     };
 
-    f32x16 acc[2][2];
+    f32x16 acc[NB][NB];
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
+    for (int i = 0; i < NB; ++i)
 #pragma unroll
-        for (int j = 0; j < 2; ++j)
+        for (int j = 0; j < NB; ++j)
 #pragma unroll
             for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
 
@@ -155,17 +162,17 @@ __global__ __launch_bounds__(256, 2) void gemm_wide(GemmArgs g, bool act, int ve
 #pragma unroll
         for (int s = 0; s < 4; ++s) {
             if (k0 + 16 * (s & 2) >= g.K) break;  // uniform: 32 zeros
-            const int at = 16 * (s & 2) + 16 * half + 8 * (s & 1);
-            bf16x8 x[2], y[2];
+            const int at = WIDE ? 16 * (s & 2) + 16 * half + 8 * (s & 1) : 16 * s + 8 * half;
+            bf16x8 x[NB], y[NB];
 #pragma unroll
-            for (int i = 0; i < 2; ++i) {
-                x[i] = *reinterpret_cast<const bf16x8 *>(&lds.a[i * 32 + l32][at]);
-                y[i] = *reinterpret_cast<const bf16x8 *>(&lds.b[wave * 64 + i * 32 + l32][at]);
+            for (int i = 0; i < NB; ++i) {
+                x[i] = *reinterpret_cast<const bf16x8 *>(&lds.a[wm + i * 32 + l32][at]);
+                y[i] = *reinterpret_cast<const bf16x8 *>(&lds.b[wn + i * 32 + l32][at]);
             }
 #pragma unroll
-            for (int mi = 0; mi < 2; ++mi)
+            for (int mi = 0; mi < NB; ++mi)
 #pragma unroll
-                for (int ni = 0; ni < 2; ++ni)
+                for (int ni = 0; ni < NB; ++ni)
                     acc[mi][ni] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x[mi], y[ni], acc[mi][ni], 0, 0, 0);
         }
         __syncthreads();
@@ -173,14 +180,14 @@ __global__ __launch_bounds__(256, 2) void gemm_wide(GemmArgs g, bool act, int ve
 
     // accumulator register r of lane l: row 8*(r/4) + 4*(l/32) + r%4, column l%32
 #pragma unroll
-    for (int ni = 0; ni < 2; ++ni) {
-        const int64_t n = n0 + wave * 64 + ni * 32 + l32;
+    for (int ni = 0; ni < NB; ++ni) {
+        const int64_t n = n0 + wn + ni * 32 + l32;
         const float bias = g.bias[min(n, g.N - 1)];
 #pragma unroll
-        for (int mi = 0; mi < 2; ++mi)
+        for (int mi = 0; mi < NB; ++mi)
 #pragma unroll
             for (int r = 0; r < 16; ++r) {
-                const int64_t m = m0 + mi * 32 + 8 * (r >> 2) + 4 * half + (r & 3);
+                const int64_t m = m0 + wm + mi * 32 + 8 * (r >> 2) + 4 * half + (r & 3);
                 if (m >= g.M || n >= g.N) continue;
                 const float z = acc[mi][ni][r] + bias;
                 if (g.C) g.C[m * g.ldc + n] = z;
@@ -194,6 +201,28 @@ __global__ __launch_bounds__(256, 2) void gemm_wide(GemmArgs g, bool act, int ve
 bool gemm_wide_fits(GemmOp op, bool ak, bool bk, GemmEpi epi, const GemmArgs &g) {
     return op == GEMM_BF16 && ak && bk && (epi == EPI_BIAS || epi == EPI_BIAS_GELU) && g.alpha == 1.0f &&
            g.M >= 32 && g.N >= 256 && g.M * g.N >= (1 << 20);
+}
+// The same for a layer of fewer than 256 columns.  With few rows its 64 x 64 tiles
+// leave most of the chip idle while they walk k, and the 32 x 32 tiles that stage
+// it at once are faster; with many those wait on their 66 KiB of LDS, two
+// workgroups a CU, and load for 512 k whatever k is.  A forward of three layers,
+// 32 x 32 tiles / these: d = 64, widths 64, 64, 32: 8192 rows 21.9 / 17.7 us, 32768
+// 61 / 20; 128, 128, 64: 4096 rows 22.5 / 22.0, 32768 115 / 35; d = 1024, 64, 64, 16:
+// 4096 rows 24 / 30, 8192 36 / 32; 250, 250, 50: 2000 rows 37 / 44, 4096 58 / 46; d =
+// 50, 50, 50, 50: 8192 rows 31 / 22; d = 784, 250, 250, 10, the last layer alone:
+// 8192 rows 54 / 58, 32768 162 / 156.
+bool gemm_narrow_fits(GemmOp op, bool ak, bool bk, GemmEpi epi, const GemmArgs &g) {
+    return op == GEMM_BF16 && ak && bk && (epi == EPI_BIAS || epi == EPI_BIAS_GELU) && g.alpha == 1.0f &&
+           g.N < 256 && (g.M >= 16384 || (g.M >= 4096 && g.M * g.N >= (3 << 17)));
+}
+
+template <int WN>
+kkm_status gemm_wide_launch(GemmEpi epi, const GemmArgs &g, hipStream_t stream) {
+    const dim3 grid((unsigned)((g.N + WN - 1) / WN), (unsigned)((g.M + WM - 1) / WM));
+    hipLaunchKernelGGL(gemm_wide<WN>, grid, dim3(256), 0, stream, g, epi == EPI_BIAS_GELU,
+                       vec_ok(g.A, g.lda, g.K) && vec_ok(g.B, g.ldb, g.K));
+    KKM_HIP(hipGetLastError());
+    return KKM_OK;
 }
 
 template <bool AK, bool BK, int KS, int EPI>
@@ -237,13 +266,8 @@ kkm_status gemm_bf16_small(bool ak, bool bk, GemmEpi epi, const GemmArgs &g, hip
 kkm_status gemm_launch(GemmOp op, bool ak, bool bk, GemmEpi epi, const GemmArgs &g,
                        hipStream_t stream) {
     if (g.M <= 0 || g.N <= 0) return KKM_OK;
-    if (gemm_wide_fits(op, ak, bk, epi, g)) {
-        const dim3 grid((unsigned)((g.N + WN - 1) / WN), (unsigned)((g.M + WM - 1) / WM));
-        hipLaunchKernelGGL(gemm_wide, grid, dim3(256), 0, stream, g, epi == EPI_BIAS_GELU,
-                           vec_ok(g.A, g.lda, g.K) && vec_ok(g.B, g.ldb, g.K));
-        KKM_HIP(hipGetLastError());
-        return KKM_OK;
-    }
+    if (gemm_wide_fits(op, ak, bk, epi, g)) return gemm_wide_launch<256>(epi, g, stream);
+    if (gemm_narrow_fits(op, ak, bk, epi, g)) return gemm_wide_launch<64>(epi, g, stream);
     if (op == GEMM_BF16) return gemm_bf16_small(ak, bk, epi, g, stream);
     const dim3 grid((unsigned)((g.N + TM - 1) / TM), (unsigned)((g.M + TM - 1) / TM));
     const dim3 blk(256);

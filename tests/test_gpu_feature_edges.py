@@ -80,3 +80,24 @@ def test_seeding_either_side_of_its_own_select(kkm, n, f, k, pad):
     """384 groups of 256 rows are the most that every workgroup selects from for
     itself; past them a launch selects."""
     test_seeding_and_lloyd_step(kkm, n, f, k, pad)
+
+
+# (n, d, h1, h2, out): layers of fewer than 256 columns at the fewest rows that
+# take the 64 x 64 tiles, columns and k around 32 and 64, rows past a whole tile
+# and past the first 32768
+@pytest.mark.parametrize("n,d,h1,h2,out,pad", [(4096, 33, 128, 130, 255, 0), (4099, 64, 129, 65, 200, 1),
+                                               (8200, 96, 64, 65, 63, 0), (16384, 31, 1, 2, 3, 0), (32800, 7, 17, 16, 33, 1),
+                                               (32768, 100, 255, 32, 64, 0)])
+def test_narrow_layers_of_many_rows(kkm, n, d, h1, h2, out, pad):
+    """The rows of a large call are those of small ones (other tiles, the same order
+    of sums) bit for bit."""
+    import torch
+    g = torch.Generator(device="cuda")
+    g.manual_seed(n + d)
+    X = torch.randn(n, d + pad, generator=g, device="cuda")[:, :d]
+    th = 0.1 * torch.randn(kkm.mlp_param_count(d, h1, h2, out), generator=g, device="cuda")
+    net = dict(h1=h1, h2=h2, out=out)
+    print("narrow layers", n, d, h1, h2, out, flush=True)
+    F = kkm.kkm_mlp_forward(th, X, **net)
+    for a in (0, 2000, n - 1001):
+        assert torch.equal(F[a:a + 1001], kkm.kkm_mlp_forward(th, X[a:a + 1001], **net))
