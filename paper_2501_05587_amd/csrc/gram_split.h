@@ -57,7 +57,10 @@ constexpr int SPB = 3 * SPP;                  // bytes of a group's slab
 constexpr int SPT = GM / SPG * SPB;           // bytes of a tile operand's slab
 
 struct SplitLds {
-    unsigned char op[2][SPT];
+    union {
+        unsigned char op[2][SPT];
+        float T[epi_lds_bytes(1) / sizeof(float)];  // the epilogue's tile
+    };
     float rn[2 * GM], rs[2 * GM];
 };
 
@@ -280,13 +283,15 @@ __device__ __forceinline__ void split_tile(const SplitTile &x, const F32Tile &sr
         for (int j = 0; j < 2; ++j)
 #pragma unroll
             for (int r = 0; r < 16; ++r) acc[i][j][r] += lo[i][j][r];
-    static_assert(sizeof(lds.op) >= epi_lds_bytes(2), "epilogue tile does not fit");
-    static_assert(sizeof(lds.op) >= epi_lds_bytes_bf16, "bfloat16 epilogue tile does not fit");
-    float *T = reinterpret_cast<float *>(&lds.op[0][0]);
+    // FP32 K and the FULL shape: the tile staged whole, as the FP32 kernel's (in
+    // halves FULL was 64 us at n = 5000, d = 32 where it is 53, and the FP32 kernel
+    // 50); bfloat16 K: in halves, which hold it whole as bfloat16
+    constexpr int HV = sizeof(OUT) == 2 ? 2 : 1;
+    static_assert(sizeof(lds.T) >= epi_lds_bytes_bf16, "bfloat16 epilogue tile does not fit");
     if (FULL && bi != bj)
-        epilogue<OUT, true, 2>(e, acc, m0, n0, false, wr, wc, lane, T, lds.rn, lds.rs);
+        epilogue<OUT, true, 1>(e, acc, m0, n0, false, wr, wc, lane, lds.T, lds.rn, lds.rs);
     else
-        epilogue<OUT, false, 2>(e, acc, m0, n0, bi == bj, wr, wc, lane, T, lds.rn, lds.rs);
+        epilogue<OUT, false, HV>(e, acc, m0, n0, bi == bj, wr, wc, lane, lds.T, lds.rn, lds.rs);
 }
 
 }  // namespace
