@@ -1080,7 +1080,6 @@ void inst_carve(void *base, const InstGeom &g, Inst *in, size_t *bytes) {
     float *P = c.take<float>((size_t)g.slots * (size_t)g.ldp);
     float *Zp = c.take<float>((size_t)g.slots * (size_t)g.nws_max);
     float *ctilde = c.take<float>((size_t)g.k);
-    (void)c.take<double>((size_t)g.nblk);
     if (bytes) *bytes = c.bytes();
     if (!in) return;
     in->n = g.n;
