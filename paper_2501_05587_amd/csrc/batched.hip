@@ -8,7 +8,7 @@
 //                 upper-triangle tiles from a device counter.  Problems are
 //                 queued costliest tile first (largest d, then largest n), so
 //                 the cheapest tiles fill the tail of the queue.
-//   3. loop       the six step kernels over a device table of the problems
+//   3. loop       the seven step kernels over a device table of the problems
 //                 still running, then a control kernel that retires the
 //                 problems whose step changed no label (or that reached
 //                 max_iter) and rewrites the table in place.  The grid sizes

@@ -213,7 +213,7 @@ bool gemm_wide_fits(GemmOp op, bool ak, bool bk, GemmEpi epi, const GemmArgs &g)
 // 8192 rows 54 / 58, 32768 162 / 156.
 bool gemm_narrow_fits(GemmOp op, bool ak, bool bk, GemmEpi epi, const GemmArgs &g) {
     return op == GEMM_BF16 && ak && bk && (epi == EPI_BIAS || epi == EPI_BIAS_GELU) && g.alpha == 1.0f &&
-           g.N < 256 && (g.M >= 16384 || (g.M >= 4096 && g.M * g.N >= (3 << 17)));
+           g.N < 256 && g.M <= 65535 * WM && (g.M >= 16384 || (g.M >= 4096 && g.M * g.N >= (3 << 17)));
 }
 
 template <int WN>

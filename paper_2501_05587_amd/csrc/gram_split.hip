@@ -14,13 +14,13 @@ __global__ __launch_bounds__(256) void split_rows(const float *X, int64_t n, int
                                                   int64_t groups, int64_t nslab, unsigned char *Xs) {
     const int lane = threadIdx.x & 63;
     const int64_t g = blockIdx.x;
-    const int64_t slab = (int64_t)blockIdx.y * 4 + (threadIdx.x >> 6);
-    if (slab >= nslab) return;
     const int r = lane >> 2, c = (lane & 3) ^ ((r >> 2) & 3);
     const int64_t row = g * SPG + r;
-    float v[8];
-    split_load(X + min(row, n - 1) * ldx, d, slab * SPK + 8 * c, v);
-    split_store(v, d, slab * SPK + 8 * c, row < n, Xs + (slab * groups + g) * SPB + lane * 16);
+    for (int64_t slab = (int64_t)blockIdx.y * 4 + (threadIdx.x >> 6); slab < nslab; slab += 4 * (int64_t)gridDim.y) {
+        float v[8];
+        split_load(X + min(row, n - 1) * ldx, d, slab * SPK + 8 * c, v);
+        split_store(v, d, slab * SPK + 8 * c, row < n, Xs + (slab * groups + g) * SPB + lane * 16);
+    }
 }
 
 // Squared norms (Gaussian; as the FP32 product's prologue) and the rows' marks,
@@ -63,8 +63,9 @@ kkm_status launch_gram_split(int32_t k_store, bool full, const F32Tile &a, const
                              unsigned char *Xs, float *nrm, hipStream_t stream) {
     const int64_t groups = split_groups(a.e.n), nslab = split_slabs(a.d);
     if (Xs) {
-        hipLaunchKernelGGL(split_rows, dim3((unsigned)groups, (unsigned)((nslab + 3) / 4)), dim3(256), 0, stream, a.X,
-                           a.e.n, a.d, a.ldx, groups, nslab, Xs);
+        const unsigned gy = (unsigned)((nslab + 3) / 4 < 65535 ? (nslab + 3) / 4 : 65535);
+        hipLaunchKernelGGL(split_rows, dim3((unsigned)groups, gy), dim3(256), 0, stream, a.X, a.e.n, a.d, a.ldx, groups,
+                           nslab, Xs);
         KKM_HIP(hipGetLastError());
     }
     hipLaunchKernelGGL(split_stats, dim3((unsigned)((a.e.n + 3) / 4)), dim3(256), 0, stream, a.X, a.e.n, a.d,

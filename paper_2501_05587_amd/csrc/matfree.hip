@@ -398,8 +398,9 @@ __global__ __launch_bounds__(256) void matfree_sweep(MfArgs a, Inst in, const in
 // n = 20000: BF16 d = 256 1.02 -> 0.38 ms, FP8 d = 256 0.94 -> 0.28 ms, FP32
 // d = 128 1.63 -> 1.03 ms and d = 256 2.66 -> 1.92 ms (the FP32 MFMA's rate).
 // Products run over the slabs in the staged kernel's order, so every kernel
-// value is bit for bit the one the stored K holds; the sums of 16 or 32 values
-// per lane go through the same compensated running sums.
+// value is the staged sweep's bit for bit (and the stored K's, but for an FP32
+// product large enough that the stored K takes it as split bfloat16); the sums of
+// 16 or 32 values per lane go through the same compensated running sums.
 constexpr int MR_WAVE = 32;  // points per wave
 
 template <int NS> constexpr int mr_rows() { return NS <= 4 ? 64 : 32; }
@@ -443,8 +444,11 @@ __global__ __launch_bounds__(256, NS <= 2 ? 3 : 2) void matfree_resident(MfArgs 
     const float sB = (a.scale && in_n) ? a.scale[my_i] : 1.f;
 
     // 16 bytes of a row.  Rows past the chunk or past n are read as the last one
-    // that exists, slabs past the row's as its first: their values are computed
-    // and left out of every sum, and no load waits on a branch.
+    // that exists: their values are computed and left out of every sum.  BF16 and
+    // FP8 rows are whole slabs: a slab past the row's is read as its first (no
+    // product takes it), and no load waits on a branch.  FP32 rows are the
+    // caller's: zeros past d, behind a branch on the alignment and the end of the
+    // row.
     auto piece = [&](int64_t row, int off) -> uint4 {
         if constexpr (PREC == KKM_F32)
             return __builtin_bit_cast(uint4, load_f32x4(a, row, off / 4));

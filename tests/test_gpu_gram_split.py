@@ -1,4 +1,4 @@
-"""The FP32 kernel matrix where its product is taken as six bfloat16 products
+"""The FP32 kernel matrix where its product is taken as eight bfloat16 products
 of three-part values: against 64 bits, in every shape and layout, and against
 the FP32 kernel for the values that are left to it.
 
