@@ -70,17 +70,17 @@ SPLIT_PRODUCTS = 8
 # recorded value; otherwise the traffic is reported as null.
 TRAFFIC = {
     "packed_sweep": {"sources": ["csrc/packed.hip", "csrc/iterate.h", "csrc/kkm_common.h"],
-                     "sha256": "091bd2b99e611b4ad75afb7a3912997b638354009902d6db0c2ec8202e3c0fc8",
-                     "n": 200000, "fetch_kib": 39622114.1, "write_kib": 4963109.8,
+                     "sha256": "43ecb67847e99e8332243761e5930158355591febfb8bc48f55df5cbb654a537",
+                     "n": 200000, "fetch_kib": 39620882.0, "write_kib": 4963096.0,
                      "fetch_scale": 1.9999, "write_scale": 1.0},
     "spmm_row_sweep": {"sources": ["csrc/iterate.hip", "csrc/iterate.h", "csrc/kkm_common.h"],
-                       "sha256": "60d57fe61d8ab1718d5ce6e3a0d8757ba4d3964110fdc851c4b02ee5b328da15",
-                       "n": 200000, "fetch_kib": 78171632.4, "write_kib": 89563.4,
+                       "sha256": "3f45ba30a78ccf94d81d38858657665da3516bd6ed5532bcf19ee15783b22667",
+                       "n": 200000, "fetch_kib": 78171198.5, "write_kib": 89573.0,
                        "fetch_scale": 1.9999, "write_scale": 1.0},
     "gram_split_mfma": {"sources": ["csrc/gram.hip", "csrc/gram_split.hip", "csrc/gram_split.h",
                                     "csrc/gram_tile.h", "csrc/kkm_common.h"],
-                        "sha256": "39ea43c1d36037e6014cfe7ed50f6cc09786922c20b96754a7d68e93b9d122db",
-                        "n": 200000, "fetch_kib": 319955168.6, "write_kib": 169139403.1,
+                        "sha256": "568dde82358989194cdfd1fc6f9d0dae8ffb90afc3a51462c6b8308552ad3935",
+                        "n": 200000, "fetch_kib": 165258237.0, "write_kib": 156251062.0,
                         "fetch_scale": 1.9999, "write_scale": 1.0},
 }
 
