@@ -191,15 +191,15 @@ TrainStep small_step(float *th, const Dims &m, const float *XB, int64_t ldx, flo
     return t;
 }
 
-kkm_status small_train_step(TrainStep t, float *am, float *av, int32_t step, double lr, double beta1,
+kkm_status small_train_step(TrainStep t, float *am, float *av, int64_t step, double lr, double beta1,
                             double beta2, double eps, hipStream_t s) {
-    if (!adam_ok(lr, beta1, beta2, eps)) {
+    if (step > INT32_MAX || !adam_ok(lr, beta1, beta2, eps)) {
         set_error("kkm_mlp_adam: bad arguments");
         return KKM_ERR_ARG;
     }
     t.am = am;
     t.av = av;
-    const AdamArgs a = adam_args(step, lr, beta1, beta2, eps);
+    const AdamArgs a = adam_args((int32_t)step, lr, beta1, beta2, eps);
     return train_step_small(t, &a, s);
 }
 
@@ -414,7 +414,7 @@ extern "C" kkm_status kkm_mlp_train(float *params, float *adam_m, float *adam_v,
         KKM_HIP(hipGetLastError());
         if (B <= kSmallBatch) {
             TrainStep t = small_step(params, m, w.XB, d, w.KB, B, B, w, loss_trace + st);
-            KKM_TRY(small_train_step(t, adam_m, adam_v, t0 + st + 1, lr, beta1, beta2, eps, s));
+            KKM_TRY(small_train_step(t, adam_m, adam_v, (int64_t)t0 + st + 1, lr, beta1, beta2, eps, s));
             continue;
         }
         KKM_TRY(loss_grad(params, m, w.XB, d, w.KB, B, B, w, w.grad, loss_trace + st, s));
@@ -466,7 +466,7 @@ extern "C" kkm_status kkm_mlp_train_fresh(float *params, float *adam_m, float *a
         if (B <= kSmallBatch) {
             TrainStep t = small_step(params, m, XB, ldx, w.KB, B, B, w, loss_trace + st);
             t.kern = BatchKernel{kernel_type, gt::epi_gamma(kernel_type, gamma), (float)coef0, degree};
-            KKM_TRY(small_train_step(t, adam_m, adam_v, t0 + st + 1, lr, beta1, beta2, eps, s));
+            KKM_TRY(small_train_step(t, adam_m, adam_v, (int64_t)t0 + st + 1, lr, beta1, beta2, eps, s));
             continue;
         }
         KKM_TRY(gram_launch(XB, B, d, ldx, kernel_type, gamma, coef0, degree, KKM_F32, KKM_F32,

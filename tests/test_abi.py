@@ -151,3 +151,14 @@ def test_batched_validation_without_device_work(lib):
     assert ws(arr(ok, ok), 2, 0, 0) >= 2 * 100 * 128 * 4
     assert ws(arr(ok), 1, 1, 1) < one          # BF16 K is half the size
     assert ws(arr(bad_k), 1, 0, 0) == 0
+
+
+def test_training_step_numbers_past_the_largest_are_refused(lib):
+    # Adam's step numbers are t0 + 1 .. t0 + steps: the first is already past int32
+    vp, cs = ctypes.c_void_p, ctypes.c_size_t
+    fake = vp(4096)
+    for B in (8, 256):
+        need = lib.kkm_mlp_train_fresh_workspace_bytes(B, 4, 5, 6, 3)
+        assert lib.kkm_mlp_train_fresh(fake, fake, fake, 4, 5, 6, 3, fake, 4, B, 1, 2147483647, 2, 1.0, 0.0, 1, 1e-3,
+                                       0.9, 0.999, 1e-8, fake, fake, cs(need), None) == -1
+        assert b"bad arguments" in lib.kkm_last_error()
