@@ -79,8 +79,8 @@ TRAFFIC = {
                        "fetch_scale": 1.9999, "write_scale": 1.0},
     "gram_split_mfma": {"sources": ["csrc/gram.hip", "csrc/gram_split.hip", "csrc/gram_split.h",
                                     "csrc/gram_tile.h", "csrc/kkm_common.h"],
-                        "sha256": "568dde82358989194cdfd1fc6f9d0dae8ffb90afc3a51462c6b8308552ad3935",
-                        "n": 200000, "fetch_kib": 165258237.0, "write_kib": 156251062.0,
+                        "sha256": "8269a00501527124e9ca53cf54bb7ba156169a558aa9860c282f4a0253c6a3af",
+                        "n": 200000, "fetch_kib": 152467332.1, "write_kib": 156250890.6,
                         "fetch_scale": 1.9999, "write_scale": 1.0},
 }
 

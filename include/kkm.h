@@ -82,7 +82,7 @@ typedef enum { KKM_EMPTY_INF = 0, KKM_EMPTY_ZERO_CENTROID = 1 } kkm_empty_policy
  *           A KKM_F32 product runs on the FP32 matrix unit or, for d >= 16 and
  *           n >= 3584 (n >= 2304 where d > 64), on the bfloat16 one with every
  *           value as the sum of three bfloat16 parts that hold all its bits
- *           (error against 64 bits no larger).  Values that are neither zero
+ *           (the bound of its error is no larger).  Values that are neither zero
  *           nor between 2^-45 and 2^50 in size, or not finite, leave the tiles
  *           of their rows (128 x 128) to the FP32 unit.  The choice depends on
  *           n, d and X alone, so every entry point and shape gives the same K

@@ -9,7 +9,7 @@
 // The products h h' have sums of their own, a slab's 32 features from zero and
 // the slabs' rounded to nearest: these products have 16 bits, so that FP32 adds a
 // few of them without rounding.  All the others are below 2^-6 of them, and the
-// roundings of their sum below 2^-29.  The two meet once, after the last slab.  So
+// roundings of their sum below 2^-29.  The two meet once, in the last slab.  So
 // a single product is rounded once, as the FP32 matrix unit rounds it, and a sum
 // less often: with one sum for all of them, a slab with one feature that both
 // rows have cost two roundings more, and sparse rows were less exact than on the
@@ -17,11 +17,16 @@
 // was off by up to 1.5 times as much.
 // Error against 64 bits, relative in norm, of X X^T, n = 3600, here / FP32 matrix
 // unit / six products with one sum a slab: normal points d = 16 3.2e-8 / 7.4e-8 /
-// 3.4e-8, d = 128 5.5e-8 / 2.0e-7 / 8.0e-8, d = 784 1.0e-7 / 4.9e-7 / 1.2e-7; one
-// entry in five not zero d = 64 2.7e-8 / 3.9e-8 / 5.1e-8, d = 784 5.3e-8 / 1.2e-7 /
-// 9.8e-8; one feature 2.5e-8 / 2.5e-8 / 3.5e-8.
+// 3.4e-8, d = 128 5.4e-8 / 2.0e-7 / 8.0e-8, d = 784 9.9e-8 / 4.9e-7 / 1.2e-7; one
+// entry in five not zero d = 64 2.9e-8 / 3.9e-8 / 5.1e-8, d = 784 5.3e-8 / 1.2e-7 /
+// 9.8e-8; one feature 2.5e-8 / 2.5e-8 / 3.5e-8.  The matrix unit sums eight products
+// at a time and cuts each off at 2^-24 of the largest one's power of two, so of few
+// features that differ by many powers of two the FP32 unit's chain is the more
+// exact where it happens to add the small ones first (feature k scaled by 4^k, d =
+// 16 5.7e-8 / 2.5e-8; log-normal values over 2^+-4, d = 64 7.1e-8 / 6.8e-8, from d =
+// 128 on 0.92 to 0.14 of it); the bound of the sum is no larger.
 //
-// n = 60000, d = 784: 25.4 -> 18.4 ms, 1.23 PFLOP/s of bfloat16 products, the
+// n = 60000, d = 784: 25.4 -> 18.7 ms, 1.21 PFLOP/s of bfloat16 products, the
 // rate that a plain bfloat16 product of 8192^3 reaches on this card (1.13).
 //
 // Values whose low parts would leave the bfloat16 range, and infinities and
@@ -31,7 +36,7 @@
 //
 // The parts are laid out once (PRE) where the workspace has room for them, else
 // split while they are staged: the same parts, so the same K bit for bit (n =
-// 60000, d = 784 18.8 / 22.2 ms, d = 128 4.7 / 5.2; n = 3584, d = 128 43 / 42 us).
+// 60000, d = 784 18.8 / 22.1 ms, d = 128 4.6 / 5.0; n = 3584, d = 128 42 / 41 us).
 //
 // Per 32-feature slab a 128 x 128 tile stages 2 x 24 KiB with direct
 // global-to-LDS loads, already in LDS order (the prologue wrote them so), single
@@ -253,6 +258,16 @@ __device__ __forceinline__ void split_tile(const SplitTile &x, const F32Tile &sr
             product(1, 1);
             mixed(0, 1);
         }
+        // the rest joins the running sum before the last slab's h h': one rounding
+        // less where those are most of it (features scaled from 2^-30 to 1, d = 128:
+        // error in norm 4.1e-8; joined after them 4.8e-8, the FP32 unit 4.5e-8)
+        if (kt + 1 == x.nslab)  // uniform
+#pragma unroll
+            for (int i = 0; i < 2; ++i)
+#pragma unroll
+                for (int j = 0; j < 2; ++j)
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) hi[i][j][r] += lo[i][j][r];
         // h h' of the slab, from zero, then rounded to nearest into the running sum:
         // the matrix unit's own additions to a long sum cut it off
 #pragma unroll
@@ -277,12 +292,6 @@ __device__ __forceinline__ void split_tile(const SplitTile &x, const F32Tile &sr
         __syncthreads();  // every read of the slab is done
     }
     f32x16(&acc)[2][2] = hi;
-#pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int j = 0; j < 2; ++j)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) acc[i][j][r] += lo[i][j][r];
     // FP32 K and the FULL shape: the tile staged whole, as the FP32 kernel's (in
     // halves FULL was 64 us at n = 5000, d = 32 where it is 53, and the FP32 kernel
     // 50); bfloat16 K: in halves, which hold it whole as bfloat16

@@ -270,3 +270,34 @@ def test_fresh_training_with_the_smaller_workspace(kkm):
         tr = kkm.kkm_mlp_train_fresh(p, m, v, X, B, kernel=kkm.GAUSS, gamma=1.0 / d, ws=ws, **net)
         out.append((p, m, v, tr))
     assert all(torch.equal(a, b) for a, b in zip(*out))
+
+
+@pytest.mark.parametrize("kind", ["growing features", "shrinking features", "log-normal", "offset"])
+@pytest.mark.parametrize("d", [16, 33, 65, 128, 784])
+def test_features_of_different_sizes(kkm, d, kind):
+    """The matrix unit sums eight products at a time, each cut off at 2^-24 of the
+    largest one's power of two, and rounds their sums and the running sum to
+    nearest (as measured on gfx950): the bound that follows, where the products
+    of a sum differ by many powers of two."""
+    import torch
+    n = 3600
+    g = torch.Generator(device="cuda")
+    g.manual_seed(d)
+    X = torch.randn(n, d, generator=g, device="cuda")
+    if kind == "growing features":
+        X = X * torch.exp2(torch.linspace(-12, 0, d, device="cuda"))
+    elif kind == "shrinking features":
+        X = X * torch.exp2(torch.linspace(0, -12, d, device="cuda"))
+    elif kind == "log-normal":
+        X = X * torch.exp2(4 * torch.randn(n, d, generator=g, device="cuda"))
+    else:
+        X = X + 10
+    print("split sizes", d, kind, flush=True)
+    K = kkm.kkm_gram(X, kernel=kkm.LINEAR)[0]
+    Xd = X.double()
+    # of a slab's h h': seven cut-offs and four roundings; per slab one addition
+    # and, at 2^-6 of it, 28 roundings of the other products' sum; those products'
+    # cut-offs (49 2^-6) and the joining of the two sums.  |h h'| <= 1.02 |x y|.
+    slabs = -(-d // 32)
+    bound = 1.02 * (11 + slabs * (1 + 28 / 64) + 49 / 64 + 1) * 2.0 ** -24 * (Xd.abs() @ Xd.abs().T)
+    assert bool(((K.double() - Xd @ Xd.T).abs() <= bound).all())
